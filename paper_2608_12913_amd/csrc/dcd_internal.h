@@ -13,12 +13,12 @@ namespace dcd {
 constexpr int kWaveSize = 64;
 constexpr int kTileTokens = 256;                     // tokens per vocabulary tile
 constexpr int kStreamRowsSmall = 64;                 // rows per workgroup up to 64 rows
-constexpr int kStreamRowsLarge = 128;                // rows per workgroup from 65 to 511 rows
+constexpr int kStreamRowsLarge = 128;                // rows per workgroup from 65 rows (bf16: to 128)
 constexpr int kWordsPerTile = kTileTokens / 32;      // candidate bit words per row and tile
 constexpr int kRowInfo = 16;                         // floats of per-row results
 constexpr int kMaxNodes = 4096;                      // nodes per sequence (staged in LDS)
-constexpr int kWideRows = 256;                       // rows per workgroup of the many-row LM-head kernel
-constexpr int kWideMinRows = 512;                    // rows from which that kernel is used
+constexpr int kCus = 256;                            // compute units of an MI355X
+constexpr int kWideMinRows = 512;                    // rows from which fp32 takes 64-row workgroups again
 constexpr int kWalkMaxGroup = 64;                    // workgroups per sequence of the spread walk
 
 // rowinfo slots (floats; the argmax is stored as an int bit pattern)
@@ -242,9 +242,13 @@ hipError_t launch_rmsnorm(const Plan &p, const Inputs &in, hipStream_t st);
 hipError_t launch_lmhead(const Plan &p, const Inputs &in, hipStream_t st);
 // advances the workspace's call count (after an LM-head launch no other kernel follows)
 hipError_t launch_advance_call(const Plan &p, hipStream_t st);
-// the many-row variant (bf16, R >= kWideMinRows): same outputs
+// the many-row variant (bf16 above kStreamRowsLarge rows): same outputs
 bool use_wide_lmhead(const Plan &p);
 hipError_t launch_lmhead_wide(const Plan &p, const Inputs &in, hipStream_t st);
+// its row shapes, 2 per translation unit (rb: row blocks per wave)
+hipError_t launch_lmhead_wide45(const Plan &p, const Inputs &in, int rb, hipStream_t st);
+hipError_t launch_lmhead_wide67(const Plan &p, const Inputs &in, int rb, hipStream_t st);
+hipError_t launch_lmhead_wide89(const Plan &p, const Inputs &in, int rb, hipStream_t st);
 // the streaming LM-head kernel in its two row shapes (p.rows_blk selects)
 hipError_t launch_lmhead_rows64(const Plan &p, const Inputs &in, hipStream_t st);
 hipError_t launch_lmhead_rows128(const Plan &p, const Inputs &in, hipStream_t st);
