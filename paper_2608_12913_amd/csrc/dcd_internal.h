@@ -9,16 +9,16 @@ namespace dcd {
 
 // LM-head tile geometry (gfx950: 64-lane waves, 16x16 MFMA blocks).  Every LM-head
 // kernel reduces its logits per vocabulary tile of kTileTokens tokens; the
-// streaming kernel has two row shapes, 64 and 128 rows per workgroup.
+// streaming kernel has row shapes of 16, 32, 48, 64 and 128 rows per workgroup.
 constexpr int kWaveSize = 64;
 constexpr int kTileTokens = 256;                     // tokens per vocabulary tile
-constexpr int kStreamRowsSmall = 64;                 // rows per workgroup up to 64 rows
-constexpr int kStreamRowsLarge = 128;                // rows per workgroup from 65 rows (bf16: to 128)
+constexpr int kStreamRowsSmall = 64;                 // its largest shape that keeps both heads' logits in registers
+constexpr int kStreamRowsLarge = 128;                // its largest shape (bf16: the most rows it takes)
 constexpr int kWordsPerTile = kTileTokens / 32;      // candidate bit words per row and tile
 constexpr int kRowInfo = 16;                         // floats of per-row results
 constexpr int kMaxNodes = 4096;                      // nodes per sequence (staged in LDS)
 constexpr int kCus = 256;                            // compute units of an MI355X
-constexpr int kWideMinRows = 512;                    // rows from which fp32 takes 64-row workgroups again
+constexpr int kWideMinRows = 512;                    // rows from which fp32 takes at most 64 rows per workgroup
 constexpr int kWalkMaxGroup = 64;                    // workgroups per sequence of the spread walk
 
 // rowinfo slots (floats; the argmax is stored as an int bit pattern)
@@ -33,7 +33,9 @@ enum ElemType { kF32 = 0, kBF16 = 1 };
 struct Plan {
     int B, N, R, V, dp, dq, dtype;
     int ntiles;        // ceil(V / kTileTokens)
-    int rows_blk;      // rows per workgroup of the streaming LM-head kernel (64 or 128)
+    int rows_blk;      // rows per workgroup of the streaming LM-head kernel (16, 32, 48, 64 or 128)
+    int wide;          // the many-row LM-head kernel runs instead (bf16)
+    int park_zp;       // the workspace has room for the 128-row shape's parked expert logits
     int nrb;           // ceil(R / rows_blk)
     int wstride;       // candidate bit words per row (ntiles * kWordsPerTile)
     float log_theta;   // ln(plaus_thresh); -inf when the mask is off
@@ -242,14 +244,16 @@ hipError_t launch_rmsnorm(const Plan &p, const Inputs &in, hipStream_t st);
 hipError_t launch_lmhead(const Plan &p, const Inputs &in, hipStream_t st);
 // advances the workspace's call count (after an LM-head launch no other kernel follows)
 hipError_t launch_advance_call(const Plan &p, hipStream_t st);
-// the many-row variant (bf16 above kStreamRowsLarge rows): same outputs
-bool use_wide_lmhead(const Plan &p);
+// the many-row variant (p.wide): same outputs
 hipError_t launch_lmhead_wide(const Plan &p, const Inputs &in, hipStream_t st);
 // its row shapes, 2 per translation unit (rb: row blocks per wave)
 hipError_t launch_lmhead_wide45(const Plan &p, const Inputs &in, int rb, hipStream_t st);
 hipError_t launch_lmhead_wide67(const Plan &p, const Inputs &in, int rb, hipStream_t st);
 hipError_t launch_lmhead_wide89(const Plan &p, const Inputs &in, int rb, hipStream_t st);
-// the streaming LM-head kernel in its two row shapes (p.rows_blk selects)
+// the streaming LM-head kernel in its row shapes (p.rows_blk selects)
+hipError_t launch_lmhead_rows16(const Plan &p, const Inputs &in, hipStream_t st);
+hipError_t launch_lmhead_rows32(const Plan &p, const Inputs &in, hipStream_t st);
+hipError_t launch_lmhead_rows48(const Plan &p, const Inputs &in, hipStream_t st);
 hipError_t launch_lmhead_rows64(const Plan &p, const Inputs &in, hipStream_t st);
 hipError_t launch_lmhead_rows128(const Plan &p, const Inputs &in, hipStream_t st);
 // proposals from the recombined heads (rows only, after launch_lmhead)

@@ -41,7 +41,10 @@ typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 
-// Row shape of this translation unit (lmhead128.hip includes this file with 128):
+// Row shape of this translation unit (lmhead16.hip, lmhead32.hip, lmhead48.hip and
+// lmhead128.hip include this file with the others):
+//   16, 32, 48 rows: the 64-row shape with fewer row blocks (stream_rows, below, says
+//             where each is used);
 //   64 rows:  4 waves of 64 tokens x 64 rows, 128-byte chunks (32 KB of weights in
 //             flight per workgroup), two workgroups per CU;
 //   128 rows: 4 waves of 64 tokens x 128 rows (128 accumulators per wave), 128-byte
@@ -55,13 +58,9 @@ typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 #ifndef DCD_STREAM_ROWS
 #define DCD_STREAM_ROWS 64
 #endif
-#if DCD_STREAM_ROWS == 64
 constexpr int NW = 4, VB = 4, CB = 128, kMinBlocks = 2;
-#elif DCD_STREAM_ROWS == 128
-constexpr int NW = 4, VB = 4, CB = 128, kMinBlocks = 2;
-#else
-#error "DCD_STREAM_ROWS must be 64 or 128"
-#endif
+static_assert(DCD_STREAM_ROWS == 16 || DCD_STREAM_ROWS == 32 || DCD_STREAM_ROWS == 48 ||
+              DCD_STREAM_ROWS == 64 || DCD_STREAM_ROWS == 128, "row shapes");
 
 constexpr int NT = NW * kWaveSize;        // threads per workgroup
 constexpr int TS = kTileTokens;           // tokens per tile
@@ -71,16 +70,18 @@ constexpr int LPR = CB / 16;              // lanes per row in a weight load inst
 constexpr int RPI = kWaveSize / LPR;      // rows per weight load instruction
 constexpr int WLOADS = 16 * VB / RPI;     // weight load instructions per wave and chunk
 constexpr int KS = CB / 64;               // MFMA k-steps per chunk
-constexpr int HLOADS = ROWS * CB / (NT * 16);  // 16-byte hidden-state loads per thread and chunk
+constexpr int HRPI = NT / LPR;            // hidden-state rows per load of the workgroup
+constexpr int HLOADS = (ROWS + HRPI - 1) / HRPI;  // 16-byte hidden-state loads per thread and chunk
+constexpr bool kHTail = ROWS % HRPI != 0;  // the last load covers more rows than there are
 constexpr int WTILE = VB * 16 * CB;       // bytes of one wave's weight chunk
 constexpr int HTILE = ROWS * CB;          // bytes of one hidden-state chunk
 constexpr int QX = LPR / RPI > 0 ? LPR / RPI : 1;  // distinct weight-row swizzles per lane
 constexpr bool kParkStats = ROWS > 64;    // expert row statistics kept in LDS across the amateur pass
-static_assert(HLOADS >= 1 && ROWS * CB == HLOADS * NT * 16, "hidden-state staging must tile");
+static_assert(ROWS % RPI == 0, "a wave's hidden-state rows of one load are all in the chunk or none");
 static_assert(CB % 64 == 0 && WLOADS * RPI == 16 * VB && LPR % RPI == 0 || RPI % LPR == 0,
               "weight chunk must tile");
 static_assert(TS == 16 * VB * NW && TS % 32 == 0 && TS <= NT, "tile = 16*VB tokens per wave");
-static_assert((NT / LPR) % LPR == 0, "hidden-state rows of one thread share a swizzle");
+static_assert(HRPI % LPR == 0, "hidden-state rows of one thread share a swizzle");
 static_assert(4 * VB <= 32, "a lane's candidate flags of a row block fit one word");
 
 // One 16-byte A fragment x one 16-byte B fragment, accumulated into c.
@@ -144,7 +145,8 @@ struct Stream {
     // c of row RPI*q + r of the wave's rows (RPI rows x CB contiguous bytes per
     // instruction); address = wave-uniform row base (scalar registers) + a 32-bit
     // lane offset.  Hidden-state loads: thread -> (row, 16-byte column) of the
-    // 64 x CB chunk; rows past R re-read row R-1 (results discarded).
+    // ROWS x CB chunk; rows past R re-read row R-1 (results discarded), rows past the
+    // chunk its last one (not staged).
     //
     // Chunk order.  Tile `tile` walks K starting at chunk (7*tile mod nch) and
     // wraps around.  Started in step, every tile would request the same 128-byte
@@ -174,7 +176,7 @@ struct Stream {
         const int hr0 = tid / LPR;
 #pragma unroll
         for (int p = 0; p < HLOADS; ++p)
-            hoff[p] = (uint32_t)(min(row0 + hr0 + p * (NT / LPR), R - 1) - row0) * rowbytes;
+            hoff[p] = (uint32_t)(min(row0 + min(hr0 + p * HRPI, ROWS - 1), R - 1) - row0) * rowbytes;
     }
 
     // In the K tail (rowbytes not a multiple of CB) a weight lane past the row end
@@ -202,7 +204,7 @@ struct Stream {
 // Lane-dependent LDS addresses (the rest are immediates).
 struct LdsAddr {
     int wst[QX];   // weight row RPI*k + wr, column wc (rows RPI*q + wr repeat every QX)
-    int hst;       // hidden-state row hr0, column hc (rows hr0 + p*NT/LPR share it)
+    int hst;       // hidden-state row hr0, column hc (rows hr0 + p*HRPI share it)
     int frag[KS];  // fragment column 4s+g of row n (rows 16vb+n and 16rb+n add constants)
 
     __device__ __forceinline__ void init() {
@@ -222,8 +224,10 @@ struct LdsAddr {
 // loaded registers before this point, so no wait is forced on loads in flight.
 __device__ __forceinline__ void stage(const Batch &b, char *hb, char *wbuf, const LdsAddr &a) {
 #pragma unroll
-    for (int p = 0; p < HLOADS; ++p)
-        st_lds(hb + a.hst + p * (NT / LPR) * CB, b.hok ? b.h[p] : u32x4{0u, 0u, 0u, 0u});
+    for (int p = 0; p < HLOADS; ++p) {
+        if (kHTail && (int)threadIdx.x / LPR + p * HRPI >= ROWS) continue;  // wave-uniform
+        st_lds(hb + a.hst + p * HRPI * CB, b.hok ? b.h[p] : u32x4{0u, 0u, 0u, 0u});
+    }
 #pragma unroll
     for (int q = 0; q < WLOADS; ++q) st_lds(wbuf + a.wst[q % QX] + (q / QX) * (QX * RPI) * CB, b.w[q]);
 }
@@ -754,8 +758,14 @@ hipError_t launch_skinny(const Plan &p, const Inputs &in, hipStream_t st) {
 hipError_t launch_lmhead_rows64(const Plan &p, const Inputs &in, hipStream_t st) { return launch_skinny(p, in, st); }
 
 hipError_t launch_lmhead(const Plan &p, const Inputs &in, hipStream_t st) {
-    if (use_wide_lmhead(p)) return launch_lmhead_wide(p, in, st);
-    return p.rows_blk == kStreamRowsLarge ? launch_lmhead_rows128(p, in, st) : launch_lmhead_rows64(p, in, st);
+    if (p.wide) return launch_lmhead_wide(p, in, st);
+    switch (p.rows_blk) {
+        case 16: return launch_lmhead_rows16(p, in, st);
+        case 32: return launch_lmhead_rows32(p, in, st);
+        case 48: return launch_lmhead_rows48(p, in, st);
+        case kStreamRowsSmall: return launch_lmhead_rows64(p, in, st);
+        default: return launch_lmhead_rows128(p, in, st);
+    }
 }
 
 hipError_t launch_advance_call(const Plan &p, hipStream_t st) {
@@ -763,7 +773,11 @@ hipError_t launch_advance_call(const Plan &p, hipStream_t st) {
     return hipGetLastError();
 }
 #else
-hipError_t launch_lmhead_rows128(const Plan &p, const Inputs &in, hipStream_t st) { return launch_skinny(p, in, st); }
+#define DCD_CAT2(a, b) a##b
+#define DCD_CAT(a, b) DCD_CAT2(a, b)
+hipError_t DCD_CAT(launch_lmhead_rows, DCD_STREAM_ROWS)(const Plan &p, const Inputs &in, hipStream_t st) {
+    return launch_skinny(p, in, st);
+}
 #endif
 
 }  // namespace dcd

@@ -759,12 +759,6 @@ int wide_row_blocks(const Plan &p) {
 
 }  // namespace
 
-// bf16 above 128 rows.  LM heads of 4096/2048 over 128,256 tokens, streaming kernel against
-// this one (one MI355X): 64 rows 240 us against about 300, 128 rows 295 against 308 (its
-// weight stream stops for each workgroup's epilogues, two of which overlap there), 160 rows
-// 480 against 325, 256 rows 505 against 400.
-bool use_wide_lmhead(const Plan &p) { return p.dtype == kBF16 && p.R > kStreamRowsLarge; }
-
 hipError_t launch_lmhead_wide(const Plan &p, const Inputs &in, hipStream_t st) {
     const int rb = wide_row_blocks(p);
     if (rb < 6) return launch_lmhead_wide45(p, in, rb, st);
