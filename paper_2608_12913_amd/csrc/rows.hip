@@ -28,9 +28,7 @@ namespace {
 
 constexpr int NT = 256;                  // threads of the finish kernel (4 waves)
 constexpr int kTileU4 = kWordsPerTile / 4;  // 16-byte bitmap words per vocabulary tile
-constexpr int kTilesPerLane = kTileTokens <= 256 ? 8 : 4;  // tiles a lane takes per pass
 static_assert(kWordsPerTile % 4 == 0, "a tile's bitmap is whole 16-byte words");
-constexpr int kPass = kWaveSize * kTilesPerLane;
 constexpr int kList = 1024;              // candidate ids gathered per round
 // masked target, sampled verification: the walk's decisions settled per row (settle_children)
 constexpr int kMembers = kList;          // mask members of a row kept in LDS
@@ -210,12 +208,34 @@ struct Smem {
     double dbl, dbl2;
 };
 
+// What a row leaves for its sequence's phase is stored word by word as relaxed atomics of
+// agent scope: these write through to where every XCD sees them, so that counting the row
+// needs no release.  (A release at agent scope writes back the XCD's whole L2; one per row,
+// they queued up: 2048 rows, finish kernel 120 us with releases, 102 without.)
+__device__ __forceinline__ void store_agent(void *dst, unsigned long long v) {
+    __hip_atomic_store((unsigned long long *)dst, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ void store_agent(float4 *dst, float4 v) {
+    const auto two = [](float lo, float hi) {
+        return (unsigned long long)__float_as_uint(hi) << 32 | __float_as_uint(lo);
+    };
+    store_agent(&dst->x, two(v.x, v.y));
+    store_agent(&dst->z, two(v.z, v.w));
+}
+// Waits until this wave's stores have completed (stores of agent scope: are visible).
+__device__ __forceinline__ void stores_done() {
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0)
+    asm volatile("" ::: "memory");
+}
+
 // Writes a row's results: rowinfo (for the sequence phase) and the optional outputs.
 __device__ __forceinline__ void write_row(const Plan &P, int row, const float (&ri)[kRowInfo],
                                           const Outputs &out) {
     float4 *dst = reinterpret_cast<float4 *>(P.rowinfo + (size_t)row * kRowInfo);
 #pragma unroll
-    for (int k = 0; k < kRowInfo / 4; ++k) dst[k] = float4{ri[4 * k], ri[4 * k + 1], ri[4 * k + 2], ri[4 * k + 3]};
+    for (int k = 0; k < kRowInfo / 4; ++k)
+        store_agent(&dst[k], float4{ri[4 * k], ri[4 * k + 1], ri[4 * k + 2], ri[4 * k + 3]});
     if (out.row_argmax) out.row_argmax[row] = __float_as_int(ri[RI_ARGMAX]);
     if (out.row_stats) {
 #pragma unroll
@@ -236,7 +256,9 @@ __device__ __forceinline__ void write_row(const Plan &P, int row, const float (&
 // its max) and D_KL(pi_p || pi_q) = sum_x pi_p (z_p - z_q) - lse_p + lse_q, whose sum
 // is merged like the expert's sum of exp (per tile: sum exp(z_p - tile max)(z_p - z_q));
 // D_KL(pi_p || pi_CD) = log Z - s D_KL(pi_p || pi_q) by the KL-decomposition lemma.
+template <int TPL>
 __device__ __forceinline__ void row_stats_full(const Plan &P, int row, int lane, const Outputs &out) {
+    constexpr int kPass = kWaveSize * TPL;
     const float4 *pr = P.partials + (size_t)row * P.ntiles;
     const float4 *yp = P.ypart + (size_t)row * P.ntiles * 2;
     LseW lp{-INFINITY, 0.f, 0.f};
@@ -244,16 +266,16 @@ __device__ __forceinline__ void row_stats_full(const Plan &P, int row, int lane,
     Best top_p{-INFINITY, -1};
     YStat st{-INFINITY, -1, -INFINITY, 0.f, 0.f, 0.f, 0.f, -1};
     for (int base = 0; base < P.ntiles; base += kPass) {
-        float4 v[kTilesPerLane], u[kTilesPerLane], w2[kTilesPerLane];
+        float4 v[TPL], u[TPL], w2[TPL];
 #pragma unroll
-        for (int k = 0; k < kTilesPerLane; ++k) {
+        for (int k = 0; k < TPL; ++k) {
             const int t = min(base + lane + k * kWaveSize, P.ntiles - 1);
             v[k] = pr[t];
             u[k] = yp[2 * t];
             w2[k] = yp[2 * t + 1];
         }
 #pragma unroll
-        for (int k = 0; k < kTilesPerLane; ++k) {
+        for (int k = 0; k < TPL; ++k) {
             if (base + lane + k * kWaveSize >= P.ntiles) continue;
             lp = lsew_merge(lp, LseW{v[k].x, v[k].y, u[k].w});
             lq = lse_merge(lq, Lse{v[k].z, v[k].w});
@@ -296,9 +318,11 @@ __device__ __forceinline__ void row_stats_full(const Plan &P, int row, int lane,
 // Row phase.  wave 0: the row's statistics; waves 1-3: the row as a draft node,
 // its token's logits under the parent row, left in sm.nodez (node_ok set) for the
 // thread that counts the row.
-template <int DT>
+// TPL: tiles a lane takes per pass (the merges run in the same order for any).
+template <int DT, int TPL>
 __device__ __forceinline__ void combine_row(const Plan &P, const Inputs &in, const Outputs &out, int row, int lane,
                             int wave, Smem &sm, bool members = false) {
+    constexpr int kPass = kWaveSize * TPL;
     const bool want_node_logits = out.node_stats != nullptr;
     if (wave >= 1) {
         if (!in.parents) return;  // rows without a tree (proposals)
@@ -356,7 +380,7 @@ __device__ __forceinline__ void combine_row(const Plan &P, const Inputs &in, con
     }
     int *list = sm.list;
     if (P.full) {
-        row_stats_full(P, row, lane, out);
+        row_stats_full<TPL>(P, row, lane, out);
         return;
     }
 
@@ -366,19 +390,19 @@ __device__ __forceinline__ void combine_row(const Plan &P, const Inputs &in, con
     const float2 *cz = P.cand + (size_t)row * P.V;
 
     // the first pass's partials, counts and bitmap words are fetched together
-    float4 v[kTilesPerLane];
-    uint4 w[kTilesPerLane][kTileU4];
+    float4 v[TPL];
+    uint4 w[TPL][kTileU4];
     // Loads are issued unconditionally from clamped indices and masked
     // afterwards (with selects), so that all of them are in flight together.
-    int c[kTilesPerLane];
-    float tm[kTilesPerLane];  // the tile's expert max (its partial)
+    int c[TPL];
+    float tm[TPL];  // the tile's expert max (its partial)
     auto issue_partials = [&](int base) {
 #pragma unroll
-        for (int k = 0; k < kTilesPerLane; ++k) v[k] = pr[min(base + lane + k * kWaveSize, P.ntiles - 1)];
+        for (int k = 0; k < TPL; ++k) v[k] = pr[min(base + lane + k * kWaveSize, P.ntiles - 1)];
     };
     auto issue_cands = [&](int base) {
 #pragma unroll
-        for (int k = 0; k < kTilesPerLane; ++k) {
+        for (int k = 0; k < TPL; ++k) {
             const int t = min(base + lane + k * kWaveSize, P.ntiles - 1);
             c[k] = tc[t];
             tm[k] = pr[t].x;
@@ -388,7 +412,7 @@ __device__ __forceinline__ void combine_row(const Plan &P, const Inputs &in, con
     };
     auto mask_partials = [&](int base) {
 #pragma unroll
-        for (int k = 0; k < kTilesPerLane; ++k) {
+        for (int k = 0; k < TPL; ++k) {
             const bool ok = base + lane + k * kWaveSize < P.ntiles;
             v[k] = ok ? v[k] : float4{-INFINITY, 0.f, -INFINITY, 0.f};
         }
@@ -400,7 +424,7 @@ __device__ __forceinline__ void combine_row(const Plan &P, const Inputs &in, con
     float thr = 0.f;
     auto mask_cands = [&](int base) {
 #pragma unroll
-        for (int k = 0; k < kTilesPerLane; ++k) {
+        for (int k = 0; k < TPL; ++k) {
             const uint32_t keep =
                 (base + lane + k * kWaveSize < P.ntiles && c[k] > 0 && tm[k] >= thr) ? ~0u : 0u;
 #pragma unroll
@@ -416,7 +440,7 @@ __device__ __forceinline__ void combine_row(const Plan &P, const Inputs &in, con
     Lse lp{-INFINITY, 0.f}, lq{-INFINITY, 0.f};
     for (int base = 0;;) {
 #pragma unroll
-        for (int k = 0; k < kTilesPerLane; ++k) {
+        for (int k = 0; k < TPL; ++k) {
             lp = lse_merge(lp, Lse{v[k].x, v[k].y});
             lq = lse_merge(lq, Lse{v[k].z, v[k].w});
         }
@@ -454,10 +478,10 @@ __device__ __forceinline__ void combine_row(const Plan &P, const Inputs &in, con
         mask_cands(base);
         // list positions in token order: tile base + lane + k * 64 is the (k * 64 +
         // lane)-th tile of the pass, so the tiles are counted k-major
-        int nset[kTilesPerLane], first[kTilesPerLane];
+        int nset[TPL], first[TPL];
         int total = 0;
 #pragma unroll
-        for (int k = 0; k < kTilesPerLane; ++k) {
+        for (int k = 0; k < TPL; ++k) {
             nset[k] = popc_tile(w[k]);
             int tk;
             first[k] = total + wave_exclusive_scan(nset[k], lane, &tk);
@@ -465,7 +489,7 @@ __device__ __forceinline__ void combine_row(const Plan &P, const Inputs &in, con
         }
         for (int lo = 0; lo < total; lo += kList) {
 #pragma unroll
-            for (int k = 0; k < kTilesPerLane; ++k)
+            for (int k = 0; k < TPL; ++k)
                 if (nset[k] > 0 && first[k] < lo + kList && first[k] + nset[k] > lo) {
                     int idx = first[k];
                     emit_ids(w[k], base + lane + k * kWaveSize, lo, &idx, list);
@@ -1689,7 +1713,7 @@ __device__ __forceinline__ void settle_children(const Plan &P, const Inputs &in,
         const double wx = at >= 0 ? w[at] : 0.0;
         if (lane == 0) {
             const double ratio = kq[k] > 0.f ? wx / (double)kq[k] : INFINITY;
-            P.wratio[r0 + kids[k]] = wx > 0.0 ? ratio : -1.0;
+            store_agent(&P.wratio[r0 + kids[k]], (unsigned long long)__double_as_longlong(wx > 0.0 ? ratio : -1.0));
         }
         const float *qk = q + (size_t)k * L;
         double part = 0.0;
@@ -1720,7 +1744,8 @@ __device__ __forceinline__ void settle_children(const Plan &P, const Inputs &in,
     const unsigned long long pos = __ballot(run > 0.0);
     const int who = cross ? __builtin_ctzll(cross) : (pos ? 63 - __builtin_clzll(pos) : -1);
     if (who < 0) {
-        if (lane == 0) P.wterm[row] = -1;  // an empty support
+        if (lane == 0)  // an empty support
+            __hip_atomic_store(&P.wterm[row], -1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     } else if (lane == who) {
         double acc = before;
         int found = -1, last = -1;
@@ -1731,14 +1756,20 @@ __device__ __forceinline__ void settle_children(const Plan &P, const Inputs &in,
                 if (acc > target) found = t;
             }
         }
-        P.wterm[row] = (int)(mlist[found >= 0 ? found : last] >> 32);
+        __hip_atomic_store(&P.wterm[row], (int)(mlist[found >= 0 ? found : last] >> 32), __ATOMIC_RELAXED,
+                           __HIP_MEMORY_SCOPE_AGENT);
     }
 }
 
 // One workgroup per row; the workgroup that finishes a sequence's last row
 // (counted in seqdone, cleared by the LM-head launch) runs the sequence phase.
-template <int DT, bool SAMPLE>
-__global__ __launch_bounds__(NT) void finish_kernel(Plan P, Inputs in, Outputs out,
+//
+// TPL: with 8 tiles per lane all partials, counts and bitmap words of a 128,256-token row
+// are in flight at once, the fastest for one row, but the registers hold one workgroup per
+// CU; with 4, three fit (sampled: two), which pays from two rows per CU on.  Finish kernel
+// with 8 and 4: 2048 masked rows 102 and 51 us, 285 rows 34 and 21, 651 untruncated 29 and 22.
+template <int DT, bool SAMPLE, int TPL>
+__global__ __launch_bounds__(NT, TPL == 8 ? 1 : SAMPLE ? 2 : 3) void finish_kernel(Plan P, Inputs in, Outputs out,
                                                     SampleInputs smp) {
     __shared__ Smem sm;
     __shared__ int last;
@@ -1749,26 +1780,22 @@ __global__ __launch_bounds__(NT) void finish_kernel(Plan P, Inputs in, Outputs o
     // the spread walk that follows starts its group's barrier count from zero
     if (SAMPLE && P.walk_group && row % P.N == 0 && tid < 2) P.walkbar[(row / P.N) * 2 + tid] = 0;
     __syncthreads();
-    combine_row<DT>(P, in, out, row, tid % kWaveSize, tid / kWaveSize, sm, SAMPLE && !P.full);
+    combine_row<DT, TPL>(P, in, out, row, tid % kWaveSize, tid / kWaveSize, sm, SAMPLE && !P.full);
     // sampled, masked: wave 1 lists the node's children while wave 0 takes the row phase
     if (SAMPLE && !P.full && tid / kWaveSize == 1) gather_children(P, in, smp, row, tid % kWaveSize, sm, dyn);
-    // count the row once all of its waves are done; thread 0 stores the node's
-    // logits, and the release half of the counting atomic publishes them together
-    // with wave 0's results and the settled walk decisions (the workgroup barrier
-    // orders those before it)
     __syncthreads();
-    if (SAMPLE && !P.full) {
-        settle_children<DT>(P, in, smp, row, tid, sm, dyn);
-        __syncthreads();
-    }
+    if (SAMPLE && !P.full) settle_children<DT>(P, in, smp, row, tid, sm, dyn);
+    if (tid == 0 && sm.node_ok) store_agent(&P.nodez[row], sm.nodez);
+    if (SAMPLE && P.walk_group) return;  // walk_kernel walks the sequence
+    // count the row once the stores of all of its waves are done: the row's results, the
+    // node's logits and the settled walk decisions (agent scope, store_agent)
+    stores_done();
+    __syncthreads();
     const int b = row / P.N;
-    if (tid == 0) {
-        if (sm.node_ok) P.nodez[row] = sm.nodez;
-        last = __hip_atomic_fetch_add(&P.seqdone[b], 1, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT) ==
-               P.N - 1;
-    }
+    if (tid == 0)
+        last = __hip_atomic_fetch_add(&P.seqdone[b], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == P.N - 1;
     __syncthreads();
-    if (!last || (SAMPLE && P.walk_group)) return;  // walk_kernel walks the sequence
+    if (!last) return;
     // acquire: the other rows of the sequence are visible from here on
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
     verify_sequence<DT, SAMPLE>(P, in, out, smp, b, tid, sm, dyn);
@@ -1785,7 +1812,7 @@ __global__ __launch_bounds__(NT) void propose_kernel(Plan P, Inputs in, ProposeO
     if (row == 0 && tid == 0) advance_call(P.ctl);  // the last kernel using the call state
     Outputs out{};
     out.row_argmax = po.argmax;
-    combine_row<DT>(P, in, out, row, tid % kWaveSize, tid / kWaveSize, sm);
+    combine_row<DT, 8>(P, in, out, row, tid % kWaveSize, tid / kWaveSize, sm);
     __syncthreads();  // the row's statistics are visible to the whole group
     const Residual target{nullptr, nullptr, nullptr, 0, nullptr, P.V};
     if (po.tokens) {
@@ -1928,33 +1955,36 @@ size_t seq_lds_bytes(int N, bool sampled, bool masked) {
     return masked && kSettleLds > walk ? kSettleLds : walk;
 }
 
+namespace {
+
+template <int DT, bool SAMPLE, int TPL>
+hipError_t finish_variant(const Plan &p, const Inputs &in, const Outputs &out, const SampleInputs &s, hipStream_t st) {
+    if constexpr (SAMPLE) {
+        // the sampled walk's LDS can exceed the default 64 KB limit of dynamic LDS
+        static const hipError_t attr = hipFuncSetAttribute((const void *)finish_kernel<DT, SAMPLE, TPL>,
+                                                           hipFuncAttributeMaxDynamicSharedMemorySize,
+                                                           (int)seq_lds_bytes(kMaxNodes, true, true));
+        if (attr != hipSuccess) return attr;
+    }
+    const size_t lds = seq_lds_bytes(p.N, SAMPLE, !p.full);
+    hipLaunchKernelGGL((finish_kernel<DT, SAMPLE, TPL>), dim3(p.R), dim3(NT), lds, st, p, in, out, s);
+    return hipGetLastError();
+}
+
+template <int DT, bool SAMPLE>
+hipError_t finish_rows(const Plan &p, const Inputs &in, const Outputs &out, const SampleInputs &s, hipStream_t st) {
+    return p.R <= kCus ? finish_variant<DT, SAMPLE, 8>(p, in, out, s, st)
+                       : finish_variant<DT, SAMPLE, 4>(p, in, out, s, st);
+}
+
+}  // namespace
+
 hipError_t launch_finish(const Plan &p, const Inputs &in, const Outputs &out,
                          const SampleInputs *smp, hipStream_t st) {
     const SampleInputs s = smp ? *smp : SampleInputs{nullptr, nullptr, nullptr};
-    const size_t lds = seq_lds_bytes(p.N, smp != nullptr, !p.full);
-    // the sampled walk's LDS can exceed the default 64 KB limit of dynamic LDS
-    static const hipError_t attr = [] {
-        const int most = (int)seq_lds_bytes(kMaxNodes, true, true);
-        hipError_t e = hipFuncSetAttribute((const void *)finish_kernel<kBF16, true>,
-                                           hipFuncAttributeMaxDynamicSharedMemorySize, most);
-        if (e == hipSuccess)
-            e = hipFuncSetAttribute((const void *)finish_kernel<kF32, true>,
-                                    hipFuncAttributeMaxDynamicSharedMemorySize, most);
-        return e;
-    }();
-    if (attr != hipSuccess) return attr;
-    if (p.dtype == kBF16) {
-        if (smp)
-            hipLaunchKernelGGL((finish_kernel<kBF16, true>), dim3(p.R), dim3(NT), lds, st, p, in, out, s);
-        else
-            hipLaunchKernelGGL((finish_kernel<kBF16, false>), dim3(p.R), dim3(NT), lds, st, p, in, out, s);
-    } else {
-        if (smp)
-            hipLaunchKernelGGL((finish_kernel<kF32, true>), dim3(p.R), dim3(NT), lds, st, p, in, out, s);
-        else
-            hipLaunchKernelGGL((finish_kernel<kF32, false>), dim3(p.R), dim3(NT), lds, st, p, in, out, s);
-    }
-    return hipGetLastError();
+    if (p.dtype == kBF16)
+        return smp ? finish_rows<kBF16, true>(p, in, out, s, st) : finish_rows<kBF16, false>(p, in, out, s, st);
+    return smp ? finish_rows<kF32, true>(p, in, out, s, st) : finish_rows<kF32, false>(p, in, out, s, st);
 }
 
 }  // namespace dcd
