@@ -1802,10 +1802,11 @@ __global__ __launch_bounds__(NT, TPL == 8 ? 1 : SAMPLE ? 2 : 3) void finish_kern
 }
 
 // Proposals from the recombined heads: one workgroup per row.  The row phase
-// (wave 0) gives the row's normalisers and argmax; then the whole group draws a
+// (wave 0) gives the row's normalisers and argmax; masked, the whole group then draws a
 // token from the row's target.  The dense target rows are written afterwards by
-// propose_probs_kernel, which spreads them over many workgroups.
-template <int DT>
+// propose_probs_kernel, which spreads them over many workgroups; untruncated,
+// propose_full_kernel does both.
+template <int DT, bool FULL>
 __global__ __launch_bounds__(NT) void propose_kernel(Plan P, Inputs in, ProposeOutputs po) {
     __shared__ Smem sm;
     const int row = blockIdx.x, tid = threadIdx.x;
@@ -1813,23 +1814,160 @@ __global__ __launch_bounds__(NT) void propose_kernel(Plan P, Inputs in, ProposeO
     Outputs out{};
     out.row_argmax = po.argmax;
     combine_row<DT, 8>(P, in, out, row, tid % kWaveSize, tid / kWaveSize, sm);
-    __syncthreads();  // the row's statistics are visible to the whole group
-    const Residual target{nullptr, nullptr, nullptr, 0, nullptr, P.V};
-    if (po.tokens) {
+    if constexpr (FULL) {
+        if (tid == 0) P.wterm[row] = 0;  // slices of the row done (propose_full_kernel)
+    } else if (po.tokens) {
+        __syncthreads();  // the row's statistics are visible to the whole group
+        const Residual target{nullptr, nullptr, nullptr, 0, nullptr, P.V};
         double total;
-        const int t = P.full ? full_scan(P, row, target, true, po.u[row], &total, tid, sm)
-                             : masked_scan(P, row, target, true, po.u[row], &total, tid, sm);
+        const int t = masked_scan(P, row, target, true, po.u[row], &total, tid, sm);
         if (tid == 0) po.tokens[row] = t;
+    }
+}
+
+constexpr int kSliceTokens = NT * 8;  // tokens of a row per workgroup of propose_full_kernel
+
+// Proposals of the untruncated target: slice blockIdx.y of row blockIdx.x.  Its dense values
+// are written (PROBS), and for the draw (DRAW) its sum is left in the row's per-tile y
+// statistics, which nothing reads any more; the workgroup that finishes a row's last slice
+// draws the row's token: the slice holding u times the total, then the token inside it (the
+// last of positive weight if rounding leaves none above it).  The sums are published as
+// relaxed agent-scope words (store_agent).
+//
+// One workgroup per row (at V = 128,256 a scan of 513 KB) took 48 us for 64 rows, after
+// which the dense rows were read again; spread over the slices, the two are one pass over y
+// and the rows written.  Whole call, 64 rows of 4096/2048-wide heads: 310 -> 292 us.
+template <bool PROBS, bool DRAW>
+__global__ __launch_bounds__(NT) void propose_full_kernel(Plan P, ProposeOutputs po, bool aligned) {
+    __shared__ WalkShared ws;
+    __shared__ int at[2];
+    const int row = blockIdx.x, slice = blockIdx.y, nslices = gridDim.y, tid = threadIdx.x;
+    const float shift = target_shift(P.rowinfo + (size_t)row * kRowInfo, P.s);
+    // (the dense y rows are padded to whole tiles, so a load of 4 tokens stays inside the row)
+    const float *yrow = P.y_full + (size_t)row * P.zstride;
+    double sum = 0.0;
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+        const int t = slice * kSliceTokens + h * (NT * 4) + tid * 4;
+        if (t >= P.V) continue;
+        const float4 yv = *reinterpret_cast<const float4 *>(yrow + t);
+        const float y[4] = {yv.x, yv.y, yv.z, yv.w};
+        float v[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            v[i] = __expf(y[i] - shift);
+            if (t + i < P.V) sum += (double)v[i];
+        }
+        if constexpr (PROBS) {
+            float *dst = po.probs + (size_t)row * P.V + t;
+            if (aligned && t + 3 < P.V) {
+                *reinterpret_cast<float4 *>(dst) = float4{v[0], v[1], v[2], v[3]};
+            } else {
+#pragma unroll
+                for (int i = 0; i < 4; ++i)
+                    if (t + i < P.V) dst[i] = v[i];
+            }
+        }
+    }
+    if constexpr (!DRAW) return;
+    double *sums = reinterpret_cast<double *>(P.ypart + (size_t)row * P.ntiles * 2);  // [nslices]
+    sum = wave_sum(sum);
+    if (tid % kWaveSize == 0) ws.wave_tot[tid / kWaveSize] = sum;
+    if (tid == 0) at[0] = at[1] = NT;
+    __syncthreads();
+    if (tid == 0) {
+        double all = 0.0;
+#pragma unroll
+        for (int w = 0; w < NT / kWaveSize; ++w) all += ws.wave_tot[w];
+        store_agent(&sums[slice], (unsigned long long)__double_as_longlong(all));
+        stores_done();
+        ws.ival[0] = __hip_atomic_fetch_add(&P.wterm[row], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) ==
+                     nslices - 1;
+    }
+    __syncthreads();
+    if (!ws.ival[0]) return;
+    // the thread among x (one per thread, in order; incl: running sums) that holds the
+    // target; slot: a word of `at` for this search.  -1: no positive weight
+    auto find = [&](double x, double start, double target, int slot) {
+        if (x > 0.0 && start + x > target) atomicMin(&at[slot], tid);
+        __syncthreads();
+        if (at[slot] == NT) {  // rounding left no crossing: the last of positive weight
+            __syncthreads();
+            if (tid == 0) at[slot] = -1;
+            __syncthreads();
+            if (x > 0.0) atomicMax(&at[slot], tid);
+            __syncthreads();
+        }
+        return at[slot];
+    };
+    auto slice_sum = [&](int i) {
+        return __longlong_as_double((long long)__hip_atomic_load((const unsigned long long *)&sums[i],
+                                                                 __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
+    };
+    // the slice: each thread takes a run of consecutive ones
+    const int per = (nslices + NT - 1) / NT;
+    const int s0 = min(nslices, tid * per), s1 = min(nslices, s0 + per);
+    double part = 0.0, total;
+    for (int i = s0; i < s1; ++i) part += slice_sum(i);
+    const double before = block_inclusive_scan(part, tid, &total, ws) - part;
+    const double target = (double)po.u[row] * total;
+    const int who = find(part, before, target, 0);
+    if (who < 0) {  // an empty support (a row that is not finite)
+        if (tid == 0) po.tokens[row] = -1;
+        return;
+    }
+    if (tid == who) {
+        double run = before, at_last = before;
+        int hit = -1, lastpos = s0;
+        for (int i = s0; i < s1 && hit < 0; ++i) {
+            const double w = slice_sum(i);
+            if (w > 0.0) {
+                lastpos = i;
+                at_last = run;
+                if (run + w > target) hit = i;
+            }
+            run += w;
+        }
+        ws.ival[1] = hit >= 0 ? hit : lastpos;
+        ws.dval = at_last;  // running sum before that slice
+    }
+    __syncthreads();
+    // the token: 8 consecutive ones per thread
+    const int t0 = ws.ival[1] * kSliceTokens + tid * 8;
+    double w[8];
+#pragma unroll
+    for (int i = 0; i < 8; i += 4) {
+        const float4 yv = *reinterpret_cast<const float4 *>(yrow + min(t0 + i, P.zstride - 4));
+        const float y[4] = {yv.x, yv.y, yv.z, yv.w};
+#pragma unroll
+        for (int j = 0; j < 4; ++j) w[i + j] = t0 + i + j < P.V ? (double)__expf(y[j] - shift) : 0.0;
+    }
+    double run = 0.0;
+#pragma unroll
+    for (int i = 0; i < 8; ++i) run += w[i];
+    const double start = ws.dval + block_inclusive_scan(run, tid, &total, ws) - run;
+    const int pick = find(run, start, target, 1);
+    if (tid == max(pick, 0)) {
+        double acc = start;
+        int found = -1, lastpos = -1;
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+            acc += w[i];
+            if (w[i] > 0.0 && found < 0) {
+                lastpos = t0 + i;
+                if (acc > target) found = t0 + i;
+            }
+        }
+        po.tokens[row] = found >= 0 ? found : lastpos;
     }
 }
 
 constexpr int kProbTokens = NT * 4;  // tokens of a row per workgroup of propose_probs_kernel
 
-// The proposal rows written densely: pi_hat(t) of row blockIdx.x for the
+// Masked, the proposal rows written densely: pi_hat(t) of row blockIdx.x for the
 // kProbTokens tokens of slice blockIdx.y, 0 off the mask.  A thread takes 4
 // consecutive tokens (one 16-byte store when the rows are 16-byte aligned); the
 // values are computed exactly as in the row phase's target.
-template <bool FULL>
 __global__ __launch_bounds__(NT) void propose_probs_kernel(Plan P, float *probs, bool aligned) {
     const int row = blockIdx.x;
     const int t0 = blockIdx.y * kProbTokens + threadIdx.x * 4;
@@ -1837,25 +1975,17 @@ __global__ __launch_bounds__(NT) void propose_probs_kernel(Plan P, float *probs,
     const float *rj = P.rowinfo + (size_t)row * kRowInfo;
     const float thr = rj[RI_THRESH], lse_p = rj[RI_LSEP], lse_q = rj[RI_LSEQ], logZ = rj[RI_LOGZ];
     float v[4] = {0.f, 0.f, 0.f, 0.f};
-    if constexpr (FULL) {
-        // the dense y rows are padded to whole tiles, so the load stays inside the row
-        const float4 yv = *reinterpret_cast<const float4 *>(P.y_full + (size_t)row * P.zstride + t0);
-        const float shift = target_shift(rj, P.s), y[4] = {yv.x, yv.y, yv.z, yv.w};
+    // bitmap words are valid only in tiles that kept candidates; the 4 tokens
+    // share a tile and a word (t0 is a multiple of 4)
+    const uint32_t word = P.tcount[(size_t)row * P.ntiles + t0 / kTileTokens] > 0
+                              ? P.bits[(size_t)row * P.wstride + (t0 >> 5)] >> (t0 & 31)
+                              : 0u;
+    const float2 *cz = P.cand + (size_t)row * P.V;
 #pragma unroll
-        for (int i = 0; i < 4; ++i) v[i] = __expf(y[i] - shift);
-    } else {
-        // bitmap words are valid only in tiles that kept candidates; the 4 tokens
-        // share a tile and a word (t0 is a multiple of 4)
-        const uint32_t word = P.tcount[(size_t)row * P.ntiles + t0 / kTileTokens] > 0
-                                  ? P.bits[(size_t)row * P.wstride + (t0 >> 5)] >> (t0 & 31)
-                                  : 0u;
-        const float2 *cz = P.cand + (size_t)row * P.V;
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            if ((word >> i & 1u) && t0 + i < P.V) {
-                const float2 c = cz[t0 + i];
-                if (c.x >= thr) v[i] = __expf((1.f + P.s) * (c.x - lse_p) - P.s * (c.y - lse_q) - logZ);
-            }
+    for (int i = 0; i < 4; ++i) {
+        if ((word >> i & 1u) && t0 + i < P.V) {
+            const float2 c = cz[t0 + i];
+            if (c.x >= thr) v[i] = __expf((1.f + P.s) * (c.x - lse_p) - P.s * (c.y - lse_q) - logZ);
         }
     }
     float *dst = probs + (size_t)row * P.V + t0;
@@ -1870,18 +2000,35 @@ __global__ __launch_bounds__(NT) void propose_probs_kernel(Plan P, float *probs,
 
 }  // namespace
 
+namespace {
+
+template <int DT>
+void propose_rows(const Plan &p, const Inputs &in, const ProposeOutputs &out, hipStream_t st) {
+    if (p.full)
+        hipLaunchKernelGGL((propose_kernel<DT, true>), dim3(p.R), dim3(NT), 0, st, p, in, out);
+    else
+        hipLaunchKernelGGL((propose_kernel<DT, false>), dim3(p.R), dim3(NT), 0, st, p, in, out);
+}
+
+}  // namespace
+
 hipError_t launch_propose(const Plan &p, const Inputs &in, const ProposeOutputs &out, hipStream_t st) {
     if (p.dtype == kBF16)
-        hipLaunchKernelGGL((propose_kernel<kBF16>), dim3(p.R), dim3(NT), 0, st, p, in, out);
+        propose_rows<kBF16>(p, in, out, st);
     else
-        hipLaunchKernelGGL((propose_kernel<kF32>), dim3(p.R), dim3(NT), 0, st, p, in, out);
-    if (out.probs) {
+        propose_rows<kF32>(p, in, out, st);
+    const bool aligned = p.V % 4 == 0 && reinterpret_cast<uintptr_t>(out.probs) % 16 == 0;
+    if (p.full) {
+        const dim3 grid(p.R, (p.V + kSliceTokens - 1) / kSliceTokens);
+        if (out.probs && out.tokens)
+            hipLaunchKernelGGL((propose_full_kernel<true, true>), grid, dim3(NT), 0, st, p, out, aligned);
+        else if (out.probs)
+            hipLaunchKernelGGL((propose_full_kernel<true, false>), grid, dim3(NT), 0, st, p, out, aligned);
+        else if (out.tokens)
+            hipLaunchKernelGGL((propose_full_kernel<false, true>), grid, dim3(NT), 0, st, p, out, aligned);
+    } else if (out.probs) {
         const dim3 grid(p.R, (p.V + kProbTokens - 1) / kProbTokens);
-        const bool aligned = p.V % 4 == 0 && reinterpret_cast<uintptr_t>(out.probs) % 16 == 0;
-        if (p.full)
-            hipLaunchKernelGGL(propose_probs_kernel<true>, grid, dim3(NT), 0, st, p, out.probs, aligned);
-        else
-            hipLaunchKernelGGL(propose_probs_kernel<false>, grid, dim3(NT), 0, st, p, out.probs, aligned);
+        hipLaunchKernelGGL(propose_probs_kernel, grid, dim3(NT), 0, st, p, out.probs, aligned);
     }
     return hipGetLastError();
 }
