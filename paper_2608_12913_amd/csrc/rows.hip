@@ -1300,24 +1300,27 @@ __device__ __forceinline__ double block_inclusive_scan(double x, int tid, double
     return before + incl;
 }
 
-// Arrival at the group's barrier number k (1, 2, ...): the workgroup's writes are
-// released at agent scope, then it waits (acquire) until all G workgroups arrived.
-// The wait is bounded; a workgroup that gives up sets the group's failure flag and
+// A word another workgroup of the group stored with store_agent, before the barrier.
+__device__ __forceinline__ double load_agent(const double *src) {
+    return __longlong_as_double((long long)__hip_atomic_load((const unsigned long long *)src, __ATOMIC_RELAXED,
+                                                             __HIP_MEMORY_SCOPE_AGENT));
+}
+
+// Arrival at the group's barrier number k (1, 2, ...), then a wait until all G workgroups
+// arrived.  The wait is bounded; a workgroup that gives up sets the group's failure flag and
 // goes on, and a workgroup that sees the flag stops waiting at once, so every
 // workgroup ends, after at most one bounded wait, even if the group never met.
-// Every wave first waits for its own stores to complete (vmcnt(0)); thread 0 then
-// releases the workgroup's writes at agent scope with its arrival and, once all
-// have arrived, acquires at agent scope for the workgroup (the caches it
-// invalidates are the CU's and its XCD's, shared by all waves of the workgroup).
-// One agent-scope fence pair per workgroup and barrier: each is a cache writeback
-// or invalidate, far too costly to issue from every wave.
+// What crosses the barrier is a few words per pass (slice sums, the next child's weights),
+// stored with store_agent and read with load_agent, so it needs no release (a write-back of
+// the XCD's L2, with the pass's residual in it) and no acquire (an invalidation of it): every
+// wave waits for its own stores, and thread 0 then counts the workgroup.  Whole sampled
+// steps, a release and an acquire per barrier (and a serial search for the next child)
+// against this: one tree of 64 nodes 290 -> 284 us, 21 trees of 31 nodes 1265 -> 1238 us.
 __device__ __forceinline__ void group_barrier(int *bar, int G, int k, WalkShared &ws) {
-    __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0): this wave's stores have landed
+    stores_done();
     __syncthreads();
     if (threadIdx.x == 0) {
-        __hip_atomic_fetch_add(bar, 1, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
-        // relaxed polling (an acquire per poll would invalidate the caches every
-        // time), one acquire fence once the count is reached
+        __hip_atomic_fetch_add(bar, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         // (the count and the failure flag are read together, as one 8-byte word)
         const unsigned long long *word = reinterpret_cast<const unsigned long long *>(bar);
         int tries = 0;
@@ -1330,7 +1333,6 @@ __device__ __forceinline__ void group_barrier(int *bar, int G, int k, WalkShared
             }
             __builtin_amdgcn_s_sleep(1);
         }
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
     }
     __syncthreads();
 }
@@ -1347,6 +1349,9 @@ __global__ __launch_bounds__(NT) void walk_kernel(Plan P, Inputs in, Outputs out
     float *s_p0 = reinterpret_cast<float *>(dyn + 2 * N), *s_qx = s_p0 + N;
     int *bar = P.walkbar + 2 * b;
     double *part = P.walkpart + (size_t)b * 2 * kWalkMaxGroup;
+    // [2][2] a pass's weights of the next child's token: its residual, and the weight before
+    // (in the sequence's per-tile y statistics, which nothing reads any more)
+    double *pub = reinterpret_cast<double *>(P.ypart + r0 * P.ntiles * 2);
     const bool lead = m == 0;  // writes the sequence's outputs
 
     // the sequence's tree, tokens and row checks (every workgroup the same)
@@ -1457,7 +1462,7 @@ __global__ __launch_bounds__(NT) void walk_kernel(Plan P, Inputs in, Outputs out
     // running sum up to its slice, so every workgroup computes the same numbers.
     auto slice_scan = [&](const double *src, double *mine, double *incl) {
         const int lane = tid % kWaveSize;
-        const double v = lane < G ? src[lane] : 0.0;
+        const double v = lane < G ? load_agent(src + lane) : 0.0;
         double x = v;
 #pragma unroll
         for (int d = 1; d < kWaveSize; d <<= 1) {
@@ -1471,7 +1476,7 @@ __global__ __launch_bounds__(NT) void walk_kernel(Plan P, Inputs in, Outputs out
     // the group total
     auto exchange = [&](double slice_sum) -> double {
         double *dst = part + (nbar % 2) * kWalkMaxGroup;
-        if (tid == 0) dst[m] = slice_sum;
+        if (tid == 0) store_agent(&dst[m], (unsigned long long)__double_as_longlong(slice_sum));
         group_barrier(bar, G, ++nbar, ws);
         if (tid < kWaveSize) {
             double mine, incl;
@@ -1484,11 +1489,22 @@ __global__ __launch_bounds__(NT) void walk_kernel(Plan P, Inputs in, Outputs out
         return tot;
     };
 
-    for (int c = 1; c < N; ++c) {
-        if (s_par[c] != cur) continue;
+    // the next child of the current node after node c (N: none), found by each wave alike
+    auto next_child = [&](int c) {
+        const int lane = tid % kWaveSize;
+        for (int c0 = c + 1; c0 < N; c0 += kWaveSize) {
+            const unsigned long long hit = __ballot(c0 + lane < N && s_par[min(c0 + lane, N - 1)] == cur);
+            if (hit) return c0 + (int)__builtin_ctzll(hit);
+        }
+        return N;
+    };
+
+    for (int c = next_child(0); c < N; c = next_child(c)) {
         // Alg. 1's accept test, taken alike by every workgroup
         if (tid == 0) {
-            const double w = xcur ? xcur[s_tok[c]] * xs : (double)s_p0[c];
+            // (after a rejection the last pass published the weight of this child's token)
+            const double *seen = pub + (nbar - 1) % 2 * 2;
+            const double w = !xcur ? (double)s_p0[c] : last_pass_applied ? load_agent(seen) * xs : load_agent(seen + 1);
             const double ratio = s_qx[c] > 0.f ? w / (double)s_qx[c] : INFINITY;
             ws.ival[3] = w > 0.0 && (double)smp.u_acc[r0 + c] <= ratio;
         }
@@ -1507,7 +1523,20 @@ __global__ __launch_bounds__(NT) void walk_kernel(Plan P, Inputs in, Outputs out
         // rejected: the residual max(0, p - pi_e^(c)), stored and summed slice by slice
         double *xout = xcur == xrow0 ? xrow1 : xrow0;
         double tot_all;
+        // the next child, if there is one: the thread that holds its token publishes its
+        // weights, and every thread touches the first lines of its run that the next pass
+        // (its proposal) or an acceptance (its target) will read
+        const int cn = next_child(c), xn = cn < N ? s_tok[cn] : -1;
+        const bool holds = xn >= t0 && xn < t1;
+        const double before = holds ? current_target().at(xn) : 0.0;
+        float touch = 0.f;
+        if (cn < N && t0 < t1) touch = smp.draft_probs[(r0 + cn) * V + t0] + P.y_full[(r0 + cn) * P.zstride + t0];
         last_rs = run_sum(smp.draft_probs + (r0 + c) * V, xout);
+        asm volatile("" ::"v"(touch));
+        if (holds) {
+            store_agent(pub + nbar % 2 * 2, (unsigned long long)__double_as_longlong(xout[xn]));
+            store_agent(pub + nbar % 2 * 2 + 1, (unsigned long long)__double_as_longlong(before));
+        }
         block_inclusive_scan(last_rs, tid, &tot_all, ws);
         const double total = exchange(tot_all);
         if (total > 0.0) {  // applied; a zero residual (rounding only) leaves p as it was
@@ -1900,10 +1929,7 @@ __global__ __launch_bounds__(NT) void propose_full_kernel(Plan P, ProposeOutputs
         }
         return at[slot];
     };
-    auto slice_sum = [&](int i) {
-        return __longlong_as_double((long long)__hip_atomic_load((const unsigned long long *)&sums[i],
-                                                                 __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
-    };
+    auto slice_sum = [&](int i) { return load_agent(sums + i); };
     // the slice: each thread takes a run of consecutive ones
     const int per = (nslices + NT - 1) / NT;
     const int s0 = min(nslices, tid * per), s1 = min(nslices, s0 + per);
