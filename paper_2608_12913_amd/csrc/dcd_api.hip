@@ -33,7 +33,9 @@ long long stream_groups(const Plan &P, int rows) {
 // fp32: the matrix cores bound it (the fp32 rate is a sixteenth of bf16's), so padding rows
 // cost as much as real ones, and so does the busiest CU's last workgroup.  With k the most
 // workgroups a CU gets, the time was within a few percent of k (1.15 RB + 0.2) + 0.3 RB for
-// RB = rows / 16, over 1 to 304 rows and three sizes of heads; the least of that is taken.
+// RB = rows / 16, over 1 to 304 rows and three sizes of heads; the least of that is taken
+// (several blocks of 48 rows took 7 to 14% longer than that: 640 rows of 17,987 tokens,
+// 4096/2048-wide proposals, 1343 us with 48, 1278 with 64; so 48 only for one block).
 // 8 rows, 256/128-wide heads, 1,024 tokens: 49 us with 64 rows, 31 with 16; 80 rows,
 // 1024/512, 32,003 tokens: 237 us with 128, 113 with 16, 139 with 64; 1 row, 4096/2048,
 // 128,256 tokens: 842 us with 64, 502 with 16; 64 rows there: 857 with 64, 1086 with 16.
@@ -63,7 +65,7 @@ int stream_rows(const Plan &P) {
         long long least = 0;
         for (int rows : shapes) {
             if (rows == kStreamRowsLarge && (P.R <= kStreamRowsSmall || P.R >= kWideMinRows)) continue;
-            if (stream_groups(P, rows) > kMaxGroups) continue;
+            if ((rows == 48 && P.R > rows) || stream_groups(P, rows) > kMaxGroups) continue;
             const long long rb = rows / 16, groups = (long long)P.ntiles * ((P.R + rows - 1) / rows);
             const long long cost = (groups + kCus - 1) / kCus * (23 * rb + 4) + 6 * rb;
             if (!least || cost <= least) best = rows, least = cost;
