@@ -1275,6 +1275,7 @@ struct WalkShared {
     double wave_tot[NT / kWaveSize];
     double dval, dval2;
     int ival[4];
+    int pick[2];
 };
 
 // inclusive scan of one double per thread over the workgroup, in thread order;
@@ -1298,6 +1299,25 @@ __device__ __forceinline__ double block_inclusive_scan(double x, int tid, double
     __syncthreads();
     *total = all;
     return before + incl;
+}
+
+// The thread that holds a draw's target: the first one that crosses it, the last of positive
+// weight if rounding leaves none, -1 if there is none either (the same answer in every
+// thread).  Both are collected between the same two barriers, so no wave can see the second
+// one's start value in place of the first one's answer and miss the barriers that follow.
+__device__ __forceinline__ int pick_thread(bool crosses, bool positive, int tid, WalkShared &ws) {
+    if (tid == 0) ws.pick[0] = NT, ws.pick[1] = -1;
+    __syncthreads();
+    const unsigned long long c = __ballot(crosses), p = __ballot(positive);
+    const int first = tid - tid % kWaveSize;
+    if (tid == first) {
+        if (c) atomicMin(&ws.pick[0], first + (int)__builtin_ctzll(c));
+        if (p) atomicMax(&ws.pick[1], first + 63 - (int)__builtin_clzll(p));
+    }
+    __syncthreads();
+    const int who = ws.pick[0] < NT ? ws.pick[0] : ws.pick[1];
+    __syncthreads();  // the words are used again by the next call
+    return who;
 }
 
 // A word another workgroup of the group stored with store_agent, before the barrier.
@@ -1590,18 +1610,7 @@ __global__ __launch_bounds__(NT) void walk_kernel(Plan P, Inputs in, Outputs out
         double tot_all;
         const double incl = block_inclusive_scan(rs, tid, &tot_all, ws);
         const double start = slice_before + incl - rs;
-        if (tid == 0) ws.ival[1] = NT;
-        __syncthreads();
-        if (rs > 0.0 && start + rs > target) atomicMin(&ws.ival[1], tid);
-        __syncthreads();
-        int who = ws.ival[1];
-        if (who == NT) {  // rounding left no crossing: the last thread of positive weight
-            if (tid == 0) ws.ival[1] = -1;
-            __syncthreads();
-            if (rs > 0.0) atomicMax(&ws.ival[1], tid);
-            __syncthreads();
-            who = ws.ival[1];
-        }
+        const int who = pick_thread(rs > 0.0 && start + rs > target, rs > 0.0, tid, ws);
         if (tid == who) {
             // the run's weights in groups (loads in flight together), added in order
             const WalkTarget wt = current_target();
@@ -1869,7 +1878,6 @@ constexpr int kSliceTokens = NT * 8;  // tokens of a row per workgroup of propos
 template <bool PROBS, bool DRAW>
 __global__ __launch_bounds__(NT) void propose_full_kernel(Plan P, ProposeOutputs po, bool aligned) {
     __shared__ WalkShared ws;
-    __shared__ int at[2];
     const int row = blockIdx.x, slice = blockIdx.y, nslices = gridDim.y, tid = threadIdx.x;
     const float shift = target_shift(P.rowinfo + (size_t)row * kRowInfo, P.s);
     // (the dense y rows are padded to whole tiles, so a load of 4 tokens stays inside the row)
@@ -1902,7 +1910,6 @@ __global__ __launch_bounds__(NT) void propose_full_kernel(Plan P, ProposeOutputs
     double *sums = reinterpret_cast<double *>(P.ypart + (size_t)row * P.ntiles * 2);  // [nslices]
     sum = wave_sum(sum);
     if (tid % kWaveSize == 0) ws.wave_tot[tid / kWaveSize] = sum;
-    if (tid == 0) at[0] = at[1] = NT;
     __syncthreads();
     if (tid == 0) {
         double all = 0.0;
@@ -1915,20 +1922,6 @@ __global__ __launch_bounds__(NT) void propose_full_kernel(Plan P, ProposeOutputs
     }
     __syncthreads();
     if (!ws.ival[0]) return;
-    // the thread among x (one per thread, in order; incl: running sums) that holds the
-    // target; slot: a word of `at` for this search.  -1: no positive weight
-    auto find = [&](double x, double start, double target, int slot) {
-        if (x > 0.0 && start + x > target) atomicMin(&at[slot], tid);
-        __syncthreads();
-        if (at[slot] == NT) {  // rounding left no crossing: the last of positive weight
-            __syncthreads();
-            if (tid == 0) at[slot] = -1;
-            __syncthreads();
-            if (x > 0.0) atomicMax(&at[slot], tid);
-            __syncthreads();
-        }
-        return at[slot];
-    };
     auto slice_sum = [&](int i) { return load_agent(sums + i); };
     // the slice: each thread takes a run of consecutive ones
     const int per = (nslices + NT - 1) / NT;
@@ -1937,7 +1930,7 @@ __global__ __launch_bounds__(NT) void propose_full_kernel(Plan P, ProposeOutputs
     for (int i = s0; i < s1; ++i) part += slice_sum(i);
     const double before = block_inclusive_scan(part, tid, &total, ws) - part;
     const double target = (double)po.u[row] * total;
-    const int who = find(part, before, target, 0);
+    const int who = pick_thread(part > 0.0 && before + part > target, part > 0.0, tid, ws);
     if (who < 0) {  // an empty support (a row that is not finite)
         if (tid == 0) po.tokens[row] = -1;
         return;
@@ -1972,7 +1965,7 @@ __global__ __launch_bounds__(NT) void propose_full_kernel(Plan P, ProposeOutputs
 #pragma unroll
     for (int i = 0; i < 8; ++i) run += w[i];
     const double start = ws.dval + block_inclusive_scan(run, tid, &total, ws) - run;
-    const int pick = find(run, start, target, 1);
+    const int pick = pick_thread(run > 0.0 && start + run > target, run > 0.0, tid, ws);
     if (tid == max(pick, 0)) {
         double acc = start;
         int found = -1, lastpos = -1;
