@@ -1864,45 +1864,50 @@ __global__ __launch_bounds__(NT) void propose_kernel(Plan P, Inputs in, ProposeO
 }
 
 constexpr int kSliceTokens = NT * 8;  // tokens of a row per workgroup of propose_full_kernel
+constexpr int kMaxSlices = 1 << 16;   // (the device's largest grid in y; above it slices are longer)
 
 // Proposals of the untruncated target: slice blockIdx.y of row blockIdx.x.  Its dense values
 // are written (PROBS), and for the draw (DRAW) its sum is left in the row's per-tile y
 // statistics, which nothing reads any more; the workgroup that finishes a row's last slice
 // draws the row's token: the slice holding u times the total, then the token inside it (the
 // last of positive weight if rounding leaves none above it).  The sums are published as
-// relaxed agent-scope words (store_agent).
+// relaxed agent-scope words (store_agent).  span: tokens per slice, a multiple of kSliceTokens
+// (more than that only where the vocabulary has more than kMaxSlices of those).
 //
 // One workgroup per row (at V = 128,256 a scan of 513 KB) took 48 us for 64 rows, after
 // which the dense rows were read again; spread over the slices, the two are one pass over y
 // and the rows written.  Whole call, 64 rows of 4096/2048-wide heads: 310 -> 292 us.
 template <bool PROBS, bool DRAW>
-__global__ __launch_bounds__(NT) void propose_full_kernel(Plan P, ProposeOutputs po, bool aligned) {
+__global__ __launch_bounds__(NT) void propose_full_kernel(Plan P, ProposeOutputs po, int span, bool aligned) {
     __shared__ WalkShared ws;
     const int row = blockIdx.x, slice = blockIdx.y, nslices = gridDim.y, tid = threadIdx.x;
     const float shift = target_shift(P.rowinfo + (size_t)row * kRowInfo, P.s);
     // (the dense y rows are padded to whole tiles, so a load of 4 tokens stays inside the row)
     const float *yrow = P.y_full + (size_t)row * P.zstride;
     double sum = 0.0;
+    const int slice0 = slice * span;
+    for (int c = 0; c < span && slice0 + c < P.V; c += kSliceTokens) {
 #pragma unroll
-    for (int h = 0; h < 2; ++h) {
-        const int t = slice * kSliceTokens + h * (NT * 4) + tid * 4;
-        if (t >= P.V) continue;
-        const float4 yv = *reinterpret_cast<const float4 *>(yrow + t);
-        const float y[4] = {yv.x, yv.y, yv.z, yv.w};
-        float v[4];
+        for (int h = 0; h < 2; ++h) {
+            const int t = slice0 + c + h * (NT * 4) + tid * 4;
+            if (t >= P.V) continue;
+            const float4 yv = *reinterpret_cast<const float4 *>(yrow + t);
+            const float y[4] = {yv.x, yv.y, yv.z, yv.w};
+            float v[4];
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            v[i] = __expf(y[i] - shift);
-            if (t + i < P.V) sum += (double)v[i];
-        }
-        if constexpr (PROBS) {
-            float *dst = po.probs + (size_t)row * P.V + t;
-            if (aligned && t + 3 < P.V) {
-                *reinterpret_cast<float4 *>(dst) = float4{v[0], v[1], v[2], v[3]};
-            } else {
+            for (int i = 0; i < 4; ++i) {
+                v[i] = __expf(y[i] - shift);
+                if (t + i < P.V) sum += (double)v[i];
+            }
+            if constexpr (PROBS) {
+                float *dst = po.probs + (size_t)row * P.V + t;
+                if (aligned && t + 3 < P.V) {
+                    *reinterpret_cast<float4 *>(dst) = float4{v[0], v[1], v[2], v[3]};
+                } else {
 #pragma unroll
-                for (int i = 0; i < 4; ++i)
-                    if (t + i < P.V) dst[i] = v[i];
+                    for (int i = 0; i < 4; ++i)
+                        if (t + i < P.V) dst[i] = v[i];
+                }
             }
         }
     }
@@ -1951,30 +1956,38 @@ __global__ __launch_bounds__(NT) void propose_full_kernel(Plan P, ProposeOutputs
         ws.dval = at_last;  // running sum before that slice
     }
     __syncthreads();
-    // the token: 8 consecutive ones per thread
-    const int t0 = ws.ival[1] * kSliceTokens + tid * 8;
+    // the token: the slice's span / NT consecutive ones per thread, 8 at a time
+    const int run_len = span / NT, t0 = ws.ival[1] * span + tid * run_len;
     double w[8];
+    auto weigh = [&](int t) {
 #pragma unroll
-    for (int i = 0; i < 8; i += 4) {
-        const float4 yv = *reinterpret_cast<const float4 *>(yrow + min(t0 + i, P.zstride - 4));
-        const float y[4] = {yv.x, yv.y, yv.z, yv.w};
+        for (int i = 0; i < 8; i += 4) {
+            const float4 yv = *reinterpret_cast<const float4 *>(yrow + min(t + i, P.zstride - 4));
+            const float y[4] = {yv.x, yv.y, yv.z, yv.w};
 #pragma unroll
-        for (int j = 0; j < 4; ++j) w[i + j] = t0 + i + j < P.V ? (double)__expf(y[j] - shift) : 0.0;
-    }
+            for (int j = 0; j < 4; ++j) w[i + j] = t + i + j < P.V ? (double)__expf(y[j] - shift) : 0.0;
+        }
+    };
     double run = 0.0;
+    for (int d = 0; d < run_len; d += 8) {
+        weigh(t0 + d);
 #pragma unroll
-    for (int i = 0; i < 8; ++i) run += w[i];
+        for (int i = 0; i < 8; ++i) run += w[i];
+    }
     const double start = ws.dval + block_inclusive_scan(run, tid, &total, ws) - run;
     const int pick = pick_thread(run > 0.0 && start + run > target, run > 0.0, tid, ws);
     if (tid == max(pick, 0)) {
         double acc = start;
         int found = -1, lastpos = -1;
+        for (int d = 0; d < run_len && found < 0; d += 8) {
+            if (run_len > 8) weigh(t0 + d);
 #pragma unroll
-        for (int i = 0; i < 8; ++i) {
-            acc += w[i];
-            if (w[i] > 0.0 && found < 0) {
-                lastpos = t0 + i;
-                if (acc > target) found = t0 + i;
+            for (int i = 0; i < 8; ++i) {
+                acc += w[i];
+                if (w[i] > 0.0 && found < 0) {
+                    lastpos = t0 + d + i;
+                    if (acc > target) found = t0 + d + i;
+                }
             }
         }
         po.tokens[row] = found >= 0 ? found : lastpos;
@@ -2038,13 +2051,15 @@ hipError_t launch_propose(const Plan &p, const Inputs &in, const ProposeOutputs 
         propose_rows<kF32>(p, in, out, st);
     const bool aligned = p.V % 4 == 0 && reinterpret_cast<uintptr_t>(out.probs) % 16 == 0;
     if (p.full) {
-        const dim3 grid(p.R, (p.V + kSliceTokens - 1) / kSliceTokens);
+        const int least = (p.V + kSliceTokens - 1) / kSliceTokens;
+        const int span = kSliceTokens * ((least + kMaxSlices - 1) / kMaxSlices);
+        const dim3 grid(p.R, (p.V + span - 1) / span);
         if (out.probs && out.tokens)
-            hipLaunchKernelGGL((propose_full_kernel<true, true>), grid, dim3(NT), 0, st, p, out, aligned);
+            hipLaunchKernelGGL((propose_full_kernel<true, true>), grid, dim3(NT), 0, st, p, out, span, aligned);
         else if (out.probs)
-            hipLaunchKernelGGL((propose_full_kernel<true, false>), grid, dim3(NT), 0, st, p, out, aligned);
+            hipLaunchKernelGGL((propose_full_kernel<true, false>), grid, dim3(NT), 0, st, p, out, span, aligned);
         else if (out.tokens)
-            hipLaunchKernelGGL((propose_full_kernel<false, true>), grid, dim3(NT), 0, st, p, out, aligned);
+            hipLaunchKernelGGL((propose_full_kernel<false, true>), grid, dim3(NT), 0, st, p, out, span, aligned);
     } else if (out.probs) {
         const dim3 grid(p.R, (p.V + kProbTokens - 1) / kProbTokens);
         hipLaunchKernelGGL(propose_probs_kernel, grid, dim3(NT), 0, st, p, out.probs, aligned);

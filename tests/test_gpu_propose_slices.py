@@ -35,3 +35,32 @@ def test_outputs_alone():
     dcd.propose(dev.problem, dev.inputs, None, None, probs, None, dev.workspace, dev.ws_bytes,
                 torch.cuda.current_stream(dev.device))
     assert np.array_equal(probs.cpu().numpy(), both["probs"])
+
+
+def test_more_tokens_than_slices_of_the_grid():
+    """2^27 + 5 tokens: more than 65,536 slices (the grid's limit in y) of 2,048, so a slice
+    holds two of those.  The states and weights are zero, so the logits are the bias: three
+    tokens share all but 134e6 exp(-30) = 2e-5 of the total alike."""
+    from paper_2608_12913_amd import dcd
+    V, d, dev = (1 << 27) + 5, 8, "cuda:0"
+    picks = [5, (1 << 26) + 2047, V - 1]
+    bf16 = dict(dtype=torch.bfloat16, device=dev)
+    bias = torch.full((V,), -30.0, device=dev)
+    bias[picks] = 0.0
+    u = torch.tensor([0.1, 0.5, 0.9], device=dev)
+    h, w = torch.zeros(3, d, **bf16), torch.zeros(V, d, **bf16)
+    prob = dcd.make_problem(1, 3, V, d, d, "bf16", 0.0, 0.5, 1.0)
+    n = dcd.workspace_bytes(prob)
+    ws = torch.zeros(n, dtype=torch.uint8, device=dev)
+    inputs = dcd.make_inputs(h, h, w, w, bias, bias, None, None)
+    tokens, argmax = (torch.full((3,), -7, dtype=torch.int32, device=dev) for _ in range(2))
+    stream = torch.cuda.current_stream()
+    dcd.propose(prob, inputs, u, tokens, None, argmax, ws, n, stream)
+    assert tokens.tolist() == picks and argmax.tolist() == [5, 5, 5]
+    probs = torch.empty(3, V, device=dev)
+    tokens.fill_(-7)
+    dcd.propose(prob, inputs, u, tokens, probs, None, ws, n, stream)
+    assert tokens.tolist() == picks
+    p = probs[:, picks].cpu().numpy()
+    np.testing.assert_allclose(p, 1 / 3, rtol=1e-4)
+    assert float((probs > 1e-3).sum()) == 9 and float(probs.min()) > 0
