@@ -19,71 +19,6 @@ size_t round_up(size_t x) { return (x + kAlign - 1) / kAlign * kAlign; }
 
 bool aligned(const void *p, size_t a) { return ((uintptr_t)p % a) == 0; }
 
-constexpr long long kMaxGroups = 0x7fffffffLL;
-
-// workgroups of the streaming kernel with `rows` rows each
-long long stream_groups(const Plan &P, int rows) {
-    return (long long)((P.ntiles + 7) / 8) * 8 * ((P.R + rows - 1) / rows);
-}
-
-// Rows per workgroup of the streaming kernel (16, 32, 48, 64 or 128), 0 for the many-row
-// kernel.  Times below: whole greedy steps on one MI355X; the results are the same in every
-// shape.
-//
-// fp32: the matrix cores bound it (the fp32 rate is a sixteenth of bf16's), so padding rows
-// cost as much as real ones, and so does the busiest CU's last workgroup.  With k the most
-// workgroups a CU gets, the time was within a few percent of k (1.15 RB + 0.2) + 0.3 RB for
-// RB = rows / 16, over 1 to 304 rows and three sizes of heads; the least of that is taken
-// (several blocks of 48 rows took 7 to 14% longer than that: 640 rows of 17,987 tokens,
-// 4096/2048-wide proposals, 1343 us with 48, 1278 with 64; so 48 only for one block).
-// 8 rows, 256/128-wide heads, 1,024 tokens: 49 us with 64 rows, 31 with 16; 80 rows,
-// 1024/512, 32,003 tokens: 237 us with 128, 113 with 16, 139 with 64; 1 row, 4096/2048,
-// 128,256 tokens: 842 us with 64, 502 with 16; 64 rows there: 857 with 64, 1086 with 16.
-//
-// bf16: the weight stream bounds it, so rows share a workgroup where the tiles alone fill
-// the chip.  Where they do not, the smallest shape that still gives every workgroup a CU of
-// its own is the fastest, as each has less to stage, read and reduce: 64 rows, 4096/2048,
-// 8,000 tokens 116 us with 64, 71 with 16; 32,003 tokens 123 and 114 (32 rows; 16 rows make
-// two rounds, 136); 128 rows, 32,003 tokens 165 with 128, 126 with 64.  Otherwise the
-// smallest shape that holds the rows: 6 untruncated rows, 128,256 tokens 253 us with 64,
-// 243 with 16 (masked: 254, 251 with 32, 258 with 16; heads of 144/64: 46 with 64 and 55 with
-// 32, as workgroups that end sooner meet at the row bounds' atomics, of 304/136: 63 and 61);
-// 80 rows there 292 with 128, 341 in two blocks of 48.
-//
-// bf16 above 128 rows: the many-row kernel, except where 16 or 32 rows give every workgroup
-// a CU of its own and a weight byte is re-read for at most 32 row blocks.  4096/2048-wide
-// heads, many-row kernel against that: 200 rows of 1,024 tokens 94 and 73 us, 512 rows 104
-// and 89, 1024 rows 128 and 121 (16 rows, 64 blocks: 135), 512 rows of 4,096 tokens 105 and
-// 96, 200 rows of 8,000 tokens 93 and 83; in two rounds it is slower (304 rows there: 100
-// and 117), with 48 or 64 rows too (107 and 117).
-// LM heads over 128,256 tokens, 128 rows against the many-row kernel: 128 rows 295 and
-// 308 us, 160 rows 480 and 325, 256 rows 505 and 400.
-int stream_rows(const Plan &P) {
-    constexpr int shapes[] = {16, 32, 48, kStreamRowsSmall, kStreamRowsLarge};
-    if (P.dtype == kF32) {
-        int best = kStreamRowsSmall;
-        long long least = 0;
-        for (int rows : shapes) {
-            if (rows == kStreamRowsLarge && (P.R <= kStreamRowsSmall || P.R >= kWideMinRows)) continue;
-            if ((rows == 48 && P.R > rows) || stream_groups(P, rows) > kMaxGroups) continue;
-            const long long rb = rows / 16, groups = (long long)P.ntiles * ((P.R + rows - 1) / rows);
-            const long long cost = (groups + kCus - 1) / kCus * (23 * rb + 4) + 6 * rb;
-            if (!least || cost <= least) best = rows, least = cost;
-        }
-        return best;
-    }
-    const bool many = P.R > kStreamRowsLarge;
-    for (int rows : shapes) {
-        const long long nrb = (P.R + rows - 1) / rows;
-        if (rows <= (many ? 32 : kStreamRowsSmall) && nrb <= 32 && P.ntiles * nrb <= kCus) return rows;
-    }
-    if (many) return 0;
-    const int least_rows = P.dp + P.dq >= 1024 ? 32 : kStreamRowsSmall;
-    for (int rows : shapes)
-        if (rows >= P.R && (P.full || rows >= least_rows)) return rows;
-    return kStreamRowsLarge;  // (the last shape holds them)
-}
-
 int make_plan(const dcd_problem *p, bool sample, Plan &P) {
     if (!p) return DCD_ERR_NULL;
     if (p->batch < 1 || p->nodes < 1 || p->vocab < 1 || p->d_expert < 1 || p->d_amateur < 1)
@@ -123,11 +58,11 @@ int make_plan(const dcd_problem *p, bool sample, Plan &P) {
     // the workspace is laid out for the row shape of 64 rows, or 128 from 65 to 511, so its
     // size does not depend on which kernel runs
     const int rows = P.R > kStreamRowsSmall && P.R < kWideMinRows ? kStreamRowsLarge : kStreamRowsSmall;
-    if (stream_groups(P, rows) > kMaxGroups) return DCD_ERR_SHAPE;
+    if (stream_groups(P.ntiles, P.R, rows) > kMaxGroups) return DCD_ERR_SHAPE;
     P.park_zp = rows == kStreamRowsLarge;
-    P.rows_blk = stream_rows(P);
-    P.wide = P.rows_blk == 0;
-    if (P.wide) P.rows_blk = rows;
+    const Route route = lmhead_route(RouteProblem{P.R, P.ntiles, P.dp, P.dq, P.dtype, P.full != 0});
+    P.wide = route.wide_rb;
+    P.rows_blk = P.wide ? rows : route.stream_rows;
     P.nrb = (P.R + P.rows_blk - 1) / P.rows_blk;
     return DCD_OK;
 }

@@ -5,20 +5,17 @@
 #include <stddef.h>
 #include <stdint.h>
 
+#include "route.h"
+
 namespace dcd {
 
 // LM-head tile geometry (gfx950: 64-lane waves, 16x16 MFMA blocks).  Every LM-head
 // kernel reduces its logits per vocabulary tile of kTileTokens tokens; the
 // streaming kernel has row shapes of 16, 32, 48, 64 and 128 rows per workgroup.
 constexpr int kWaveSize = 64;
-constexpr int kTileTokens = 256;                     // tokens per vocabulary tile
-constexpr int kStreamRowsSmall = 64;                 // its largest shape that keeps both heads' logits in registers
-constexpr int kStreamRowsLarge = 128;                // its largest shape (bf16: the most rows it takes)
 constexpr int kWordsPerTile = kTileTokens / 32;      // candidate bit words per row and tile
 constexpr int kRowInfo = 16;                         // floats of per-row results
 constexpr int kMaxNodes = 4096;                      // nodes per sequence (staged in LDS)
-constexpr int kCus = 256;                            // compute units of an MI355X
-constexpr int kWideMinRows = 512;                    // rows from which fp32 takes at most 64 rows per workgroup
 constexpr int kWalkMaxGroup = 64;                    // workgroups per sequence of the spread walk
 
 // rowinfo slots (floats; the argmax is stored as an int bit pattern)
@@ -27,14 +24,12 @@ enum {
     RI_THRESH = 8, RI_ARGMAX = 9, RI_ARGMAX_P = 10, RI_KL_PQ = 11, RI_KL_PCD = 12
 };
 
-enum ElemType { kF32 = 0, kBF16 = 1 };
-
 // Everything a launch needs, resolved on the host.
 struct Plan {
     int B, N, R, V, dp, dq, dtype;
     int ntiles;        // ceil(V / kTileTokens)
     int rows_blk;      // rows per workgroup of the streaming LM-head kernel (16, 32, 48, 64 or 128)
-    int wide;          // the many-row LM-head kernel runs instead (bf16)
+    int wide;          // row blocks per wave of the many-row LM-head kernel, which runs instead (bf16; 0: it does not)
     int park_zp;       // the workspace has room for the 128-row shape's parked expert logits
     int nrb;           // ceil(R / rows_blk)
     int wstride;       // candidate bit words per row (ntiles * kWordsPerTile)

@@ -43,7 +43,7 @@ typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 
 // Row shape of this translation unit (lmhead16.hip, lmhead32.hip, lmhead48.hip and
 // lmhead128.hip include this file with the others):
-//   16, 32, 48 rows: the 64-row shape with fewer row blocks (stream_rows, below, says
+//   16, 32, 48 rows: the 64-row shape with fewer row blocks (route.h says
 //             where each is used);
 //   64 rows:  4 waves of 64 tokens x 64 rows, 128-byte chunks (32 KB of weights in
 //             flight per workgroup), two workgroups per CU;

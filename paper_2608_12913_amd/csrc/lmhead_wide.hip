@@ -7,7 +7,7 @@
 // 128-byte chunks of every row, two k-steps each.  Weights (whole chunks) and hidden
 // states (half chunks, one k-step) load straight into two rings of LDS stages
 // (global_load_lds) while earlier ones are multiplied.  TR is chosen per problem
-// (wide_row_blocks).
+// (wide_row_blocks in route.h).
 //
 // Two waves share a SIMD, one of each row half (wave w and w + 4), and take turns: a
 // k-step is a slot of LDS reads and a slot of MFMAs, and the second half of the waves
@@ -755,28 +755,8 @@ hipError_t DCD_WIDE_LAUNCH(const Plan &p, const Inputs &in, int rb, hipStream_t 
 }
 
 #if DCD_WIDE_LO == 8
-namespace {
-
-// Row blocks per wave (TR = 32 * RB rows per workgroup): the workgroups run in rounds of
-// one per CU, and a round takes about as long as RB row blocks and a constant part (the
-// weights' share of a chunk, prologue, epilogues).  Over 132 to 2048 rows and vocabularies of
-// 4,096 to 128,256 tokens the choice was within 4% of the best of the six shapes, mostly
-// within 1%; the worst fixed shape is up to 2.5 times slower.
-int wide_row_blocks(const Plan &p) {
-    int best = 0;
-    long long best_cost = 0;
-    for (int rb = 4; rb <= 9; ++rb) {
-        const long long groups = (long long)p.ntiles * ((p.R + 32 * rb - 1) / (32 * rb));
-        const long long cost = ((groups + kCus - 1) / kCus) * (2 * rb + 3);
-        if (!best || cost < best_cost) best = rb, best_cost = cost;
-    }
-    return best;
-}
-
-}  // namespace
-
 hipError_t launch_lmhead_wide(const Plan &p, const Inputs &in, hipStream_t st) {
-    const int rb = wide_row_blocks(p);
+    const int rb = p.wide;
     if (rb < 6) return launch_lmhead_wide45(p, in, rb, st);
     return rb < 8 ? launch_lmhead_wide67(p, in, rb, st) : launch_lmhead_wide89(p, in, rb, st);
 }
