@@ -741,7 +741,11 @@ hipError_t launch_variant(const Plan &p, const Inputs &in, hipStream_t st) {
 
 template <int DT, bool FULL>
 hipError_t launch_dt_full(const Plan &p, const Inputs &in, hipStream_t st) {
-    return p.nrb == 1 ? launch_variant<DT, FULL, true>(p, in, st) : launch_variant<DT, FULL, false>(p, in, st);
+    if (p.nrb == 1) return launch_variant<DT, FULL, true>(p, in, st);
+    if constexpr (DT == kBF16 && ROWS == kStreamRowsLarge)
+        return hipErrorInvalidValue;  // (bf16 above 128 rows: another kernel or shape)
+    else
+        return launch_variant<DT, FULL, false>(p, in, st);
 }
 
 // the untruncated target (plaus_thresh = 0) has its own kernels: dense logits, no candidates

@@ -730,10 +730,13 @@ template <int RB, bool FULL>
 hipError_t launch_rb_full(const Plan &p, const Inputs &in, hipStream_t st) {
     const int nrt = (p.R + Geo<RB>::TR - 1) / Geo<RB>::TR;
     const int groups = ((p.ntiles + 7) / 8) * 8 * nrt;
-    if (nrt == 1)
-        hipLaunchKernelGGL((lmhead_wide_kernel<RB, FULL, true>), dim3(groups), dim3(NT), 0, st, p, in);
-    else
-        hipLaunchKernelGGL((lmhead_wide_kernel<RB, FULL, false>), dim3(groups), dim3(NT), 0, st, p, in);
+    if constexpr (RB > kStreamRowsLarge / 32) {  // (fewer rows than one tile of those: the streaming kernel)
+        if (nrt == 1) {
+            hipLaunchKernelGGL((lmhead_wide_kernel<RB, FULL, true>), dim3(groups), dim3(NT), 0, st, p, in);
+            return hipGetLastError();
+        }
+    }
+    hipLaunchKernelGGL((lmhead_wide_kernel<RB, FULL, false>), dim3(groups), dim3(NT), 0, st, p, in);
     return hipGetLastError();
 }
 
