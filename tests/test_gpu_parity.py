@@ -7,6 +7,7 @@ import pytest
 import oracle
 from paper_2608_12913_amd import synth
 from tests import parity
+from tests.routes import route_of
 
 torch = pytest.importorskip("torch")
 pytestmark = pytest.mark.gpu
@@ -84,18 +85,20 @@ def test_ragged_hidden_and_rows():
 
 @pytest.mark.parametrize("seed", range(2))
 def test_many_rows_ragged(seed):
-    # 9 sequences x 64 nodes = 576 rows: the many-row LM-head kernel (256-row tiles,
-    # the last one ragged), a ragged vocabulary and a K tail (200 = 3 chunks + 8 bf16)
+    # 9 sequences x 64 nodes = 576 rows: the many-row LM-head kernel (128-row tiles, the
+    # last one half full), a ragged vocabulary and a K tail (200 = 3 chunks + 8 bf16)
     case = synth.make_case("b8_batch32x64", 30 + seed, B=9, V=4099, dp=512, dq=200)
+    assert route_of(case) == ("wide", 4)
     _check_greedy(case, _greedy_tokens(case), f"many rows seed {seed}")
 
 
 @pytest.mark.parametrize("theta", [0.1, 0.0])
 def test_many_rows_tiny_hidden_and_vocabulary(theta):
     # the many-row kernel's extreme tails: 8- and 24-element rows (one K chunk, most of
-    # it past the row end) and a vocabulary of one full tile plus one token
-    case = synth.make_case("b8_batch32x64", 33, B=9, V=257, dp=8, dq=24, theta=theta)
-    assert case.R == 576
+    # it past the row end) and a vocabulary of 15 full tiles plus one token, about the
+    # smallest that goes there at 576 rows
+    case = synth.make_case("b8_batch32x64", 33, B=9, V=3841, dp=8, dq=24, theta=theta)
+    assert case.R == 576 and route_of(case) == ("wide", 4)
     _check_greedy(case, _greedy_tokens(case), f"many rows, tiny rows and vocabulary, theta {theta}")
 
 
@@ -114,8 +117,10 @@ def test_mask_and_strength_settings(theta, s):
 @pytest.mark.parametrize("theta,s", [(1.0, 0.5), (0.1, 0.0), (0.3, 2.0), (0.001, 1.0), (0.0, 0.5), (0.0, 2.0)])
 def test_mask_and_strength_settings_many_rows(theta, s):
     # 576 rows: the many-row LM-head kernel under every mask width and strength, and
-    # without the mask (its untruncated epilogue)
-    case = synth.make_case("b8_batch32x64", 12, B=9, V=2000, dp=256, dq=128)
+    # without the mask (its untruncated epilogue).  The oracle's members at theta 0.001 put
+    # 6 rows within the ambiguity gates (6.76 allowed; 7 with 4,000 tokens)
+    case = synth.make_case("b8_batch32x64", 12, B=9, V=3600, dp=256, dq=128)
+    assert route_of(case, theta) == ("wide", 4)
     tokens = _greedy_tokens(case, theta=theta, s=s)
     _check_greedy(case, tokens, f"many rows theta={theta} s={s}", theta=theta, s=s)
 
@@ -135,9 +140,8 @@ def test_untruncated_target_fp32_ragged_k():
 
 
 @pytest.mark.parametrize("B,theta", [(4, 0.1), (8, 0.1), (4, 0.0), (8, 0.0)])
-def test_fp32_128_row_tiles(B, theta):
-    # 100 and 200 rows go to the streaming kernel's 128-row workgroups (one row
-    # block with non-temporal weight loads, two with cached ones), fp32 with K tails
+def test_fp32_100_and_200_rows(B, theta):
+    # 7 and 13 row blocks of the streaming kernel's 16-row shape, fp32 with K tails
     case = synth.make_case("tiny_chain8", 24 + B, B=B, N=25, V=777, dp=100, dq=36, theta=theta)
     _check_greedy(case, _greedy_tokens(case), f"fp32 {case.R} rows theta={theta}")
 
@@ -183,13 +187,13 @@ def test_exact_integer_logits_theta_one():
 
 def test_exact_integer_logits_many_rows():
     """The same exactness through the many-row LM-head kernel: 9 sequences of 64 nodes
-    (576 rows, the last 256-row tile ragged), a ragged vocabulary, two K chunks of the
+    (576 rows, the last 128-row tile half full), a ragged vocabulary, two K chunks of the
     expert rows and one of the amateur rows.  The theta = 1 mask (the tokens tied at the
     expert max), the argmax, the expert max and the walk must match exactly."""
     rng = np.random.default_rng(15)
-    V = 3001
+    V = 4001
     case = synth.make_case("b8_batch32x64", 15, B=9, V=V, dp=128, dq=64)
-    assert case.R == 576
+    assert case.R == 576 and route_of(case) == ("wide", 4)
     for name, d in (("hp", 128), ("hq", 64)):
         setattr(case, name, synth.bf16_bits(rng.integers(-2, 3, (case.R, d)).astype(np.float32)))
     case.wp = synth.bf16_bits(rng.integers(-1, 2, (V, 128)).astype(np.float32))
@@ -237,12 +241,12 @@ def test_exact_integer_logits_untruncated_expert_top1():
 
 def test_exact_integer_logits_untruncated_many_rows():
     """theta = 0 through the many-row kernel with exact integer logits: the expert max
-    ties across vocabulary tiles and across the two token halves of a tile, so the
+    ties across vocabulary tiles and across the token waves of a tile (64 each), so the
     expert's top-1 (the lowest tied token) and the argmax are compared exactly."""
     rng = np.random.default_rng(16)
-    V = 3001
+    V = 4001
     case = synth.make_case("b8_batch32x64", 16, B=9, V=V, dp=128, dq=64, theta=0.0)
-    assert case.R == 576
+    assert case.R == 576 and route_of(case) == ("wide", 4)
     for name, d in (("hp", 128), ("hq", 64)):
         setattr(case, name, synth.bf16_bits(rng.integers(-1, 2, (case.R, d)).astype(np.float32)))
     case.wp = synth.bf16_bits(rng.integers(-1, 2, (V, 128)).astype(np.float32))
@@ -254,8 +258,8 @@ def test_exact_integer_logits_untruncated_many_rows():
     g = _runner().from_case(case, tokens).run("greedy")
     zp = oracle.eval_rows(case.hp, case.hq, case.wp, case.wq, case.bias, case.bias, theta=0.0,
                           s=case.s, want_logits=True)["zp"]
-    cross = sum(len(set(np.flatnonzero(z == z.max()) // 128)) > 1 for z in zp)
-    assert cross >= 20, "the case must tie the expert max across token halves"
+    cross = sum(len(set(np.flatnonzero(z == z.max()) // 64)) > 1 for z in zp)
+    assert cross >= 20, "the case must tie the expert max across token waves"
     assert np.array_equal(g["row_argmax_expert"], o["row_diag"][:, oracle.RD_ARGMAX_P])
     assert np.array_equal(g["row_argmax"], o["row_argmax"])
     assert np.array_equal(g["accept_len"], o["accept_len"])
@@ -292,7 +296,8 @@ def test_bias_variants(which, rows):
     if rows == "few":
         case = synth.make_case("b8_tree64", 70, N=20, depth=4, max_children=4, V=1500, dp=128, dq=64)
     else:
-        case = synth.make_case("b8_batch32x64", 71, B=9, V=1500, dp=128, dq=64)
+        case = synth.make_case("b8_batch32x64", 71, B=9, V=3900, dp=128, dq=64)
+        assert route_of(case) == ("wide", 4)
     zero = np.zeros(case.V, np.float32)
     if which == "separate":
         bp, bq = case.bias, (0.5 * case.bias - 0.25).astype(np.float32)
@@ -526,8 +531,8 @@ def test_sampled_trees_many_rows(seed, theta, s):
     """Sampled verification of 9 trees of 64 nodes (576 rows): the many-row LM-head
     kernel feeding the walk decisions settled per row."""
     case = synth.make_case("s8_chain16x8", 40 + seed, B=9, N=64, tree="tree", depth=6,
-                           max_children=4, V=2500, dp=256, dq=128, theta=theta, s=s)
-    assert case.R == 576 and case.dtype == "bf16"
+                           max_children=4, V=3900, dp=256, dq=128, theta=theta, s=s)
+    assert case.R == 576 and case.dtype == "bf16" and route_of(case) == ("wide", 4)
     probs, tokens = _sampled_tree_setup(case)
     g, o = _check_sample(case, probs, tokens, f"sampled trees, many rows, seed {seed}")
     _say(f"sampled trees, many rows, seed {seed}: accept lengths {g['accept_len'].tolist()}")
@@ -732,11 +737,9 @@ def test_full_b8_tree64_sampled(theta):
 @pytest.mark.slow
 @pytest.mark.parametrize("theta", [0.1, 0.0])
 def test_full_b8_batch32x64(theta):
-    # theta 0.1: the many-row kernel; theta 0: the streaming kernel's 64-row shape
-    # with 32 row blocks per tile.  Eight sequences spread over the batch (rows in
-    # every 256-row tile of the many-row kernel) are compared in full; their draft
-    # trees hold a full-depth path copying the oracle's argmax.  Elsewhere the
-    # tokens are random.
+    # the many-row kernel.  Eight sequences spread over the batch (rows in every row
+    # tile) are compared in full; their draft trees hold a full-depth path copying the
+    # oracle's argmax.  Elsewhere the tokens are random.
     case = synth.make_case("b8_batch32x64", 0, theta=theta)
     seqs = [0, 5, 9, 14, 18, 23, 27, 31]
     rows = np.concatenate([np.arange(b * 64, b * 64 + 64) for b in seqs])

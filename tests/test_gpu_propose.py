@@ -6,6 +6,7 @@ import pytest
 import oracle
 from paper_2608_12913_amd import synth
 from tests import parity
+from tests.routes import route_of
 
 torch = pytest.importorskip("torch")
 pytestmark = pytest.mark.gpu
@@ -79,19 +80,22 @@ def test_propose_128_row_shape(theta):
     row for its own amateur epilogue and writes the y rows the proposals are read
     from), with a ragged row block."""
     rng = np.random.default_rng(64)
-    case = synth.make_case("s8_chain16x8", 64, B=12, N=8, V=3001, dp=256, dq=128, theta=theta)
+    case = synth.make_case("s8_chain16x8", 64, B=12, N=8, V=33025, dp=256, dq=128, theta=theta)
+    assert route_of(case) == ("stream", 128)
     case.wp, case.wq = _drafter_heads(case, rng)
     u = rng.random(case.R).astype(np.float32)
     _check(case, u, f"128-row shape theta {theta}")
 
 
+@pytest.mark.parametrize("B,V,rb", [(65, 4099, 4), (33, 21767, 5), (24, 32769, 6)])
 @pytest.mark.parametrize("theta", [0.0, 0.1])
-def test_propose_many_rows(theta):
-    """520 rows: the many-row LM-head kernel (untruncated: the dense y rows the
-    proposals are read from, written over the expert logits), a ragged row tile."""
+def test_propose_many_rows(B, V, rb, theta):
+    """520, 264 and 192 rows: the many-row LM-head kernel (untruncated: the dense y rows the
+    proposals are read from, written from registers with 4 row blocks per wave, and over the
+    expert logits parked there with more), a ragged row tile or exactly one."""
     rng = np.random.default_rng(65)
-    case = synth.make_case("s8_chain16x8", 65, B=65, N=8, V=3001, dp=256, dq=128, theta=theta)
-    assert case.R == 520
+    case = synth.make_case("s8_chain16x8", 65, B=B, N=8, V=V, dp=256, dq=128, theta=theta)
+    assert route_of(case) == ("wide", rb)
     case.wp, case.wq = _drafter_heads(case, rng)
     u = rng.random(case.R).astype(np.float32)
     _check(case, u, f"many rows theta {theta}")

@@ -1,6 +1,6 @@
 """CPU model of the addresses of the many-row LM-head kernel (csrc/lmhead_wide.hip:
-workgroup -> tile mapping, Stream::init, load, request, zero_tail, the ring positions and the
-fragment reads): for every row shape, wave, lane, load and stage, global accesses stay inside
+workgroup -> tile mapping, Stream::init, load, request, zero_tail, the ring positions, the
+fragment reads and the untruncated epilogue's dense rows): for every row shape, wave, lane, load and stage, global accesses stay inside
 their operand, 32-bit lane offsets are exact, LDS accesses stay inside a stage, the loads
 fill a stage, each fragment read finds the column the swizzle put there, no stage is filled
 while a wave may still read it, and each is waited for before it is read."""
@@ -167,3 +167,25 @@ def test_ring_schedule(rb, nch):
             for (fop, j), (fs, fst) in fills.items():
                 if fop == op and j > i and fst == stage:
                     assert fs > slot  # the next fill of the stage is requested in a later slot
+
+
+@pytest.mark.parametrize("rb", SHAPES)
+@pytest.mark.parametrize("R,V", [(129, 13057), (155, 300), (520, 4099), (576, 257), (2048, 2500)])
+def test_untruncated_dense_row_accesses_stay_in_bounds(R, V, rb):
+    """The untruncated epilogue's 16-byte accesses to the dense rows [R][tiles * 256]: parked
+    expert logits and y stored where the row exists, loads from rows clamped to the last one."""
+    g = _geo(rb)
+    zstride = (V + TT - 1) // TT * TT
+    b, vb, lane = np.meshgrid(np.arange(rb), np.arange(4), LANE, indexing="ij")
+    stored = np.zeros((R, zstride // 4), np.int32)
+    for tile, row0 in _tiles(R, V, g["TR"]):
+        for wave in range(8):
+            wt, G = wave % 4, wave // 4
+            row = row0 + G * 16 * rb + 16 * b + lane % 16
+            col = tile * TT + 64 * wt + 4 * (lane // 16) + 16 * vb
+            assert np.all(col % 4 == 0) and np.all(col + 4 <= zstride)
+            load = np.minimum(row, R - 1).astype(np.int64) * zstride + col
+            assert np.all(load >= 0) and np.all(load + 4 <= R * zstride)
+            ok = row < R
+            np.add.at(stored, (row[ok], col[ok] // 4), 1)
+    assert np.all(stored == 1)  # every 16 bytes of every row by one lane
