@@ -218,8 +218,11 @@ def main():
     nodes_per_s = R / (ms_step * 1e-3)
     kbytes = lmhead_bytes(case)
     flops = 2 * R * (case.dp + case.dq) * case.V
-    # many rows (bf16, with or without the mask) go to the compute-shaped LM-head kernel
-    kernel = "lmhead_wide_kernel" if case.dtype == "bf16" and R > 128 else "lmhead_kernel"
+    # many rows (bf16, with or without the mask) go to the compute-shaped LM-head kernel, unless
+    # 16 or 32 rows per workgroup put every tile and row block on a CU of its own (csrc/route.h)
+    tiles, blocks = -(-case.V // 256), [-(-R // rows) for rows in (16, 32)]
+    small = any(n <= 32 and tiles * n <= 256 for n in blocks)
+    kernel = "lmhead_wide_kernel" if case.dtype == "bf16" and R > 128 and not small else "lmhead_kernel"
     ridge = MFMA_BF16_PEAK_TFLOPS * 1e12 / (HBM_PEAK_GBS * 1e9)
     # committed counters: per kernel and workload, and per mode and theta where they
     # differ from the workload's own

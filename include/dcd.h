@@ -172,8 +172,9 @@ typedef struct {                 /* device pointers, written by the call        
  * elements).
  * The workspace holds per-tile softmax partials, the candidate logits that may
  * fall inside the plausibility mask (theta > 0) or, with theta = 0 (every token in
- * the support), a dense row of y = (1+s) z_p - s z_q per row (the expert logits as
- * well from 65 to 511 rows) and two rows of V doubles per sequence for the
+ * the support), a dense row of y = (1+s) z_p - s z_q per row, from 65 to 511 rows
+ * another one (expert logits, where the kernel that runs keeps them there; the size
+ * does not depend on which does) and two rows of V doubles per sequence for the
  * residuals of sampled verification, and per-row results; it is O(B*N*V) bytes
  * (at most about 8.1 bytes per row and vocabulary entry).  The size depends on the
  * problem, so a workspace sized for one problem may be too small for another.

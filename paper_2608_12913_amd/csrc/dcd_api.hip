@@ -55,8 +55,8 @@ int make_plan(const dcd_problem *p, bool sample, Plan &P) {
     P.zstride = P.ntiles * kTileTokens;
     P.s = p->cd_strength;
     P.inv_T = sample ? (float)(1.0 / (double)p->temperature) : 1.f;
-    // the workspace is laid out for the row shape of 64 rows, or 128 from 65 to 511, so its
-    // size does not depend on which kernel runs
+    // the workspace is laid out for the row shape of 64 rows, or 128 from 65 to 511 (with room for
+    // its parked expert logits), so its size does not depend on which kernel runs
     const int rows = P.R > kStreamRowsSmall && P.R < kWideMinRows ? kStreamRowsLarge : kStreamRowsSmall;
     if (stream_groups(P.ntiles, P.R, rows) > kMaxGroups) return DCD_ERR_SHAPE;
     P.park_zp = rows == kStreamRowsLarge;

@@ -1,6 +1,7 @@
-// LM-head projection for more rows than the streaming kernel's 64 (bf16), with the
-// same epilogues (Alg. 1 "parallel model evaluation", the per-tile pieces of Eq. (1);
-// with the plausibility mask of Sec. 2.1 or, at theta = 0, the untruncated target).
+// LM-head projection for more rows than the streaming kernel's 128 (bf16; route.h has the
+// small vocabularies that stay with that one), with the same epilogues (Alg. 1 "parallel
+// model evaluation", the per-tile pieces of Eq. (1); with the plausibility mask of Sec. 2.1
+// or, at theta = 0, the untruncated target).
 //
 // Tile.  A workgroup owns 256 tokens x TR = 32*RB rows; its 8 waves form a 4 x 2 grid
 // of 64 tokens x 16*RB rows (4 x RB blocks of v_mfma_f32_16x16x32_bf16).  K is walked in

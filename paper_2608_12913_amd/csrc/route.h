@@ -23,8 +23,8 @@ struct RouteProblem {
 };
 
 // One of the two is 0: rows per workgroup of the streaming kernel (16, 32, 48, 64 or 128), or
-// row blocks per wave of the many-row kernel (4 to 9: 32 rows per workgroup each).  The results
-// are the same in every shape.  Times below: whole greedy steps on one MI355X.
+// row blocks per wave of the many-row kernel (4 to 9: 32 rows per workgroup each).  Times below:
+// whole greedy steps on one MI355X.
 struct Route {
     int stream_rows, wide_rb;
 };
@@ -100,9 +100,12 @@ inline int fp32_stream_rows(const RouteProblem &p) {
 // 8,000 tokens 116 us with 64, 71 with 16; 32,003 tokens 123 and 114 (32 rows; 16 rows make
 // two rounds, 136); 128 rows, 32,003 tokens 165 with 128, 126 with 64.  Otherwise the
 // smallest shape that holds the rows: 6 untruncated rows, 128,256 tokens 253 us with 64,
-// 243 with 16 (masked: 254, 251 with 32, 258 with 16; heads of 144/64: 46 with 64 and 55 with
-// 32, as workgroups that end sooner meet at the row bounds' atomics, of 304/136: 63 and 61);
-// 80 rows there 292 with 128, 341 in two blocks of 48.
+// 243 with 16; 80 rows there 292 with 128, 341 in two blocks of 48.  Masked, 32 or more rows, and
+// in narrow heads 64, as workgroups that end sooner meet at the row bounds' atomics.  128,256
+// tokens, masked, 1, 17 and 33 rows with 32 (48 for 33 rows) against 64: heads of 144/64 (208
+// columns) 54, 44, 42 and 44, 44, 41 us; 304/136 58, 53, 54 and 58, 55, 54; 448/192 42, 45, 52 and 48,
+// 51, 53; 656/272 (928) 78, 78, 81 and 80, 78, 78; 768/384 59, 63, 68 and 64, 68, 69; 1024/512 74, 77, 81
+// and 77, 80, 82; 4096/2048 within 1%.  The line at 1024 columns lies where none was slower any more.
 //
 // bf16 above 128 rows: the many-row kernel, except where 16 or 32 rows give every workgroup
 // a CU of its own and a weight byte is re-read for at most 32 row blocks.  4096/2048-wide

@@ -318,7 +318,9 @@ __device__ __forceinline__ void row_stats_full(const Plan &P, int row, int lane,
 // Row phase.  wave 0: the row's statistics; waves 1-3: the row as a draft node,
 // its token's logits under the parent row, left in sm.nodez (node_ok set) for the
 // thread that counts the row.
-// TPL: tiles a lane takes per pass (the merges run in the same order for any).
+// TPL: tiles a lane takes per pass.  A lane merges the partials of its tiles in the same order for
+// any; the mask members of a row are listed per pass, so over more than 64 * TPL tiles they fall on
+// other lanes and log Z is added in another order.
 template <int DT, int TPL>
 __device__ __forceinline__ void combine_row(const Plan &P, const Inputs &in, const Outputs &out, int row, int lane,
                             int wave, Smem &sm, bool members = false) {
