@@ -22,8 +22,8 @@
 //
 // What bounds it, measured on the 2048-row batch of 4096/2048-wide heads over 128,256
 // tokens (LM head alone; 4 waves of 128 x 128 before): 3.16 -> 2.64 ms, 1.02 -> 1.22
-// PFLOP/s epilogues included (a library matrix product of the expert head alone reaches
-// 1.24 on the same card and inputs, 1.58 on zeros: the clock falls under load).  Timing
+// PFLOP/s epilogues included (a library matrix product of the expert head alone reaches 1.24
+// to 1.31 on such cards and inputs, 1.59 on zeros: the clock falls under load).  Timing
 // copies: without the loads 1.89 ms, without the MFMAs 2.20, every load an L2 hit 2.58.
 // 285 rows: 0.69 -> 0.43 ms, 651 rows: 1.37 -> 1.14 ms.  Measured and not kept: the lines
 // of a later chunk pulled into L2 by one of the workgroups that share them (+6%), K walks
