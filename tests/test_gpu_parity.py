@@ -72,13 +72,13 @@ def test_tiny_chain8_fp32(seed):
 
 @pytest.mark.parametrize("seed", range(3))
 def test_small_tree_bf16_ragged_vocab(seed):
-    # 4099 = 16 full 256-token tiles + 3; 128 rows = 2 row blocks
+    # 4099 = 16 full 256-token tiles + 3; 128 rows = 8 full row blocks of 16
     case = synth.make_case("b8_tree64", seed, B=2, V=4099, dp=512, dq=256)
     _check_greedy(case, _greedy_tokens(case), f"small tree seed {seed}")
 
 
 def test_ragged_hidden_and_rows():
-    # K tails (520 and 136 are not multiples of 64 elements) and 70 rows (64 + 6)
+    # K tails (520 and 136 are not multiples of 64 elements) and 70 rows (4 blocks of 16, and 6)
     case = synth.make_case("b8_tree64", 7, N=70, V=1000, dp=520, dq=136)
     _check_greedy(case, _greedy_tokens(case), "ragged K and rows")
 
@@ -128,7 +128,7 @@ def test_mask_and_strength_settings_many_rows(theta, s):
 @pytest.mark.parametrize("seed", range(2))
 def test_untruncated_target_ragged(seed):
     # theta = 0: every token is in the support (dense-logit path); 16 full tiles + 3
-    # tokens, 2 row blocks
+    # tokens, 8 row blocks of 16
     case = synth.make_case("b8_tree64", 20 + seed, B=2, V=4099, dp=512, dq=256, theta=0.0)
     g, _, _ = _check_greedy(case, _greedy_tokens(case), f"untruncated ragged seed {seed}")
     assert np.all(g["row_stats"][:, oracle.RS_COUNT] == case.V)
